@@ -1,6 +1,7 @@
-"""Thin ctypes binding of libleoam.so: same names as the C entry points.
+"""Thin binding of libleoam.so: same names as the C entry points.
 
-Argument marshalling only.  Tensors are torch CUDA tensors (device memory and
+Argument marshalling only: the entry points of a decode step through _bind.so
+(csrc/bind.cpp), the others through ctypes.  Tensors are torch CUDA tensors (device memory and
 the current HIP stream come from torch; nothing else does).  If the library
 has not been built, importing this module raises: there is no fallback path.
 """
@@ -118,10 +119,27 @@ def _p(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
+    """The stream's handle; None: the current stream of the current device (torch.cuda.current_stream() builds a
+    Stream object around it: 3 us against 0.2)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _load_bind():
+    path = os.path.join(_HERE, "_bind.so")
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
+                          "(or python paper_2506_20187_amd/build.py) first")
+    from . import _bind
+    _bind.setup(Shape, _p, _stream, *(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in (
+        "chunk_score", "chunk_score_pin", "kv_chunk_abstract_append", "chunk_topk_select",
+        "sparse_chunk_attention_decode", "chunk_select_attention_decode")))
+    return _bind
+
+
+_bind = _load_bind()
 
 
 def _check(status: int, where: str) -> None:
@@ -136,8 +154,8 @@ def kv_chunk_abstract_build(shape: Shape, K, chunk_off, n_chunks, abstract, stre
 
 def kv_chunk_abstract_append(shape: Shape, K, chunk_off, n_chunks, chunk_size: int, abstract, status=None,
                              stream=None) -> None:
-    _check(_lib.kv_chunk_abstract_append(ctypes.byref(shape), _p(K), _p(chunk_off), _p(n_chunks), int(chunk_size),
-                                         _p(abstract), _p(status), _stream(stream)), "kv_chunk_abstract_append")
+    _check(_bind.kv_chunk_abstract_append(shape, K, chunk_off, n_chunks, int(chunk_size), abstract, status,
+                                          stream), "kv_chunk_abstract_append")
 
 
 def chunk_tree_refine(shape: Shape, q, K, abstract, chunk_size: int, k_tokens: int, max_rounds: int, node_cap: int,
@@ -150,8 +168,8 @@ def chunk_tree_refine(shape: Shape, q, K, abstract, chunk_size: int, k_tokens: i
 
 
 def chunk_score_pin(shape: Shape, n_chunks, sink_chunks: int, tail_chunks: int, score_ub, stream=None) -> None:
-    _check(_lib.chunk_score_pin(ctypes.byref(shape), _p(n_chunks), int(sink_chunks), int(tail_chunks), _p(score_ub),
-                                _stream(stream)), "chunk_score_pin")
+    _check(_bind.chunk_score_pin(shape, n_chunks, int(sink_chunks), int(tail_chunks), score_ub, stream),
+           "chunk_score_pin")
 
 
 def kv_chunk_compress(shape: Shape, K, V, chunk_off, n_chunks, four_bit, kblob, vblob, qmeta, total_bytes=None,
@@ -202,24 +220,21 @@ def leoam_tree_evaluations(n_tokens: int, n_chunks: int, rho: float) -> float:
 
 
 def chunk_score(shape: Shape, q, abstract, n_chunks, score_ub, score_lb=None, stream=None) -> None:
-    _check(_lib.chunk_score(ctypes.byref(shape), _p(q), _p(abstract), _p(n_chunks), _p(score_ub), _p(score_lb),
-                            _stream(stream)), "chunk_score")
+    _check(_bind.chunk_score(shape, q, abstract, n_chunks, score_ub, score_lb, stream), "chunk_score")
 
 
 def chunk_topk_select(shape: Shape, score_ub, chunk_off, n_chunks, max_chunks: int, token_budget: int, sel_idx,
                       sel_count, sel_tokens=None, workspace=None, stream=None) -> None:
     nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(_lib.chunk_topk_select(ctypes.byref(shape), _p(score_ub), _p(chunk_off), _p(n_chunks), int(max_chunks),
-                                  int(token_budget), _p(sel_idx), _p(sel_count), _p(sel_tokens), _p(workspace),
-                                  nbytes, _stream(stream)), "chunk_topk_select")
+    _check(_bind.chunk_topk_select(shape, score_ub, chunk_off, n_chunks, int(max_chunks), int(token_budget), sel_idx,
+                                   sel_count, sel_tokens, workspace, nbytes, stream), "chunk_topk_select")
 
 
 def sparse_chunk_attention_decode(shape: Shape, q, K, V, chunk_off, n_chunks, sel_idx, sel_count, softmax_scale,
                                   out, lse, workspace, stream=None, qmeta=None) -> None:
     nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(_lib.sparse_chunk_attention_decode(ctypes.byref(shape), _p(q), _p(K), _p(V), _p(qmeta), _p(chunk_off), _p(n_chunks),
-                                              _p(sel_idx), _p(sel_count), ctypes.c_float(softmax_scale), _p(out),
-                                              _p(lse), _p(workspace), nbytes, _stream(stream)),
+    _check(_bind.sparse_chunk_attention_decode(shape, q, K, V, qmeta, chunk_off, n_chunks, sel_idx, sel_count,
+                                               softmax_scale, out, lse, workspace, nbytes, stream),
            "sparse_chunk_attention_decode")
 
 
@@ -227,11 +242,9 @@ def chunk_select_attention_decode(shape: Shape, score_ub, q, K, V, chunk_off, n_
                                   token_budget: int, softmax_scale, sel_idx, sel_count, sel_tokens, out, lse, workspace,
                                   stream=None, qmeta=None) -> None:
     nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(_lib.chunk_select_attention_decode(ctypes.byref(shape), _p(score_ub), _p(q), _p(K), _p(V), _p(qmeta),
-                                              _p(chunk_off), _p(n_chunks), int(max_chunks), int(token_budget),
-                                              ctypes.c_float(softmax_scale), _p(sel_idx), _p(sel_count), _p(sel_tokens),
-                                              _p(out), _p(lse), _p(workspace), nbytes, _stream(stream)),
-           "chunk_select_attention_decode")
+    _check(_bind.chunk_select_attention_decode(shape, score_ub, q, K, V, qmeta, chunk_off, n_chunks, int(max_chunks),
+                                               int(token_budget), softmax_scale, sel_idx, sel_count, sel_tokens, out, lse,
+                                               workspace, nbytes, stream), "chunk_select_attention_decode")
 
 
 STATIC_SCRATCH_BYTES = 4 << 20
