@@ -181,6 +181,10 @@ __device__ __forceinline__ void encode8(const float* x, float zero, float scale,
     }
 }
 
+// The codes are written past the caches (non-temporal): nothing in this launch reads them, and lines that
+// still wait to be written back slow down whatever runs next (abstracts of the store straight after its
+// compression, 256K tokens: 60 -> 52 us; the compression itself is unchanged).
+typedef uint32_t code8_t __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ __forceinline__ void encode_row(const uint4& raw, float zero, float scale, float inv, bool four,
                                            unsigned char* dst_row, int c16) {
@@ -191,15 +195,15 @@ __device__ __forceinline__ void encode_row(const uint4& raw, float zero, float s
         // four nibbles make an integer below 65536: exact in float
         const float h0 = fmaf(r[3], 4096.f, fmaf(r[2], 256.f, fmaf(r[1], 16.f, r[0])));
         const float h1 = fmaf(r[7], 4096.f, fmaf(r[6], 256.f, fmaf(r[5], 16.f, r[4])));
-        *reinterpret_cast<uint32_t*>(dst_row + 4 * c16) = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        __builtin_nontemporal_store((uint32_t)h0 | ((uint32_t)h1 << 16), reinterpret_cast<uint32_t*>(dst_row + 4 * c16));
     } else {
-        uint2 w = make_uint2(0u, 0u);
+        code8_t w = {0u, 0u};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             w.x = __builtin_amdgcn_cvt_pk_u8_f32(r[e], e, w.x);
             w.y = __builtin_amdgcn_cvt_pk_u8_f32(r[4 + e], e, w.y);
         }
-        *reinterpret_cast<uint2*>(dst_row + 8 * c16) = w;
+        __builtin_nontemporal_store(w, reinterpret_cast<code8_t*>(dst_row + 8 * c16));
     }
 }
 

@@ -17,32 +17,6 @@
 
 namespace leoam {
 
-// the 8 codes of this lane's channels [8*c16, 8*c16+8) of the row at `row`
-__device__ __forceinline__ void load_codes(const unsigned char* row, int bits, int c16, float* x) {
-    if (bits == 8) {
-        const uint2 w = *reinterpret_cast<const uint2*>(row + 8 * c16);
-        x[0] = (float)(w.x & 0xffu); x[1] = (float)((w.x >> 8) & 0xffu);
-        x[2] = (float)((w.x >> 16) & 0xffu); x[3] = (float)(w.x >> 24);
-        x[4] = (float)(w.y & 0xffu); x[5] = (float)((w.y >> 8) & 0xffu);
-        x[6] = (float)((w.y >> 16) & 0xffu); x[7] = (float)(w.y >> 24);
-    } else {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(row + 4 * c16);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = (float)((w >> (4 * e)) & 0xfu);
-    }
-}
-__device__ __forceinline__ void load_codes_int(const unsigned char* row, int bits, int c16, int* x) {
-    if (bits == 8) {
-        const uint2 w = *reinterpret_cast<const uint2*>(row + 8 * c16);
-        x[0] = w.x & 0xffu; x[1] = (w.x >> 8) & 0xffu; x[2] = (w.x >> 16) & 0xffu; x[3] = w.x >> 24;
-        x[4] = w.y & 0xffu; x[5] = (w.y >> 8) & 0xffu; x[6] = (w.y >> 16) & 0xffu; x[7] = w.y >> 24;
-    } else {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(row + 4 * c16);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = (w >> (4 * e)) & 0xfu;
-    }
-}
-
 // ---- outward rounding double -> binary16 ------------------------------------
 __device__ __forceinline__ float float_next_up(float f) {
     uint32_t u = float_to_bits(f);
@@ -62,21 +36,127 @@ __device__ __forceinline__ uint16_t half_ceil_bits(double x) {
     if ((float)h < f) hb = half_next_up(hb);                         // smallest half >= f
     return hb;
 }
-__device__ __forceinline__ uint16_t half_floor_bits(double x) { return (uint16_t)(half_ceil_bits(-x) ^ 0x8000u); }
 
 // ---------------------------------------------------------------------------
 // abstract of the stored values (paper Sec. 4.3), rounded outward to binary16.
 // scale >= 0, so max over tokens of scale*code+zero = scale*max(code)+zero: the
 // reduction runs on integer codes (exact), one evaluation per channel at the end.
 // ---------------------------------------------------------------------------
-constexpr int kQAbsWaves = 4;
+constexpr int kQAbsWaves = 1;
+constexpr int kQAbsLoads = 4;      // 1 KiB loads of a wave in flight
 
+typedef uint16_t code2_t __attribute__((ext_vector_type(2)));      // two codes: one register
+__device__ __forceinline__ uint32_t codes_max(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(code2_t, a), __builtin_bit_cast(code2_t, b)));
+}
+__device__ __forceinline__ uint32_t codes_min(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(code2_t, a), __builtin_bit_cast(code2_t, b)));
+}
+template <bool kMax> __device__ __forceinline__ uint32_t codes_extreme(uint32_t a, uint32_t b) {
+    return kMax ? codes_max(a, b) : codes_min(a, b);
+}
+// with the pair of codes n lanes further on in the 16-lane row (n = 4 or 8, cyclic)
+template <bool kMax, int kRor> __device__ __forceinline__ uint32_t codes_ror(uint32_t v) {
+    return codes_extreme<kMax>(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + kRor, 0xf, 0xf, true));
+}
+// rows_extreme_quad for pairs of codes: row 0 returns the extremes of a over the four rows, row 1 those
+// of c, row 2 those of b, row 3 those of d
+template <bool kMax> __device__ __forceinline__ uint32_t codes_rows_quad(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    float fa = bits_to_float(a), fb = bits_to_float(b), fc = bits_to_float(c), fd = bits_to_float(d);
+    permlane32_swap(fa, fb);
+    permlane32_swap(fc, fd);
+    float u = bits_to_float(codes_extreme<kMax>(float_to_bits(fa), float_to_bits(fb)));
+    float w = bits_to_float(codes_extreme<kMax>(float_to_bits(fc), float_to_bits(fd)));
+    permlane16_swap(u, w);
+    return codes_extreme<kMax>(float_to_bits(u), float_to_bits(w));
+}
+
+// Largest and smallest code of every channel over `n` rows of a chunk.  A lane reads 16 bytes of a row,
+// so a wave-wide load covers 8 (8-bit) or 16 (4-bit) contiguous rows.  Two channels share every maximum
+// and minimum: in each 16-bit half of a dword the codes up to code p are kept (one mask, none for the
+// topmost), whose extremes have code p's extreme as their leading bits.  Afterwards the row groups are
+// folded across the 16-lane rows (lane swaps, which also leave a quarter of the registers) and inside
+// them (rotations), so that every lane ends up with four neighbouring channels of one bound: kmax or
+// kmin (`is_min`), channels ch .. ch+3.
+template <int kBits>
+__device__ __forceinline__ void code_extremes(const unsigned char* base, int n, int* code, int* ch, bool* is_min) {
+    constexpr int kRowBytes = LEOAM_D * kBits / 8;
+    constexpr int kLanes = kRowBytes / 16;                      // lanes that share a row
+    constexpr int kRows = LEOAM_WAVE / kLanes;                  // rows of a wave-wide load
+    constexpr int kPairs = 16 / kBits;                          // codes in half a dword
+    const int lane = lane_id(), j = lane % kLanes, rgrp = lane / kLanes;
+    uint32_t mx[kPairs][4], mn[kPairs][4];
+#pragma unroll
+    for (int p = 0; p < kPairs; ++p)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            mx[p][d] = 0u;
+            mn[p][d] = 0xffffffffu;
+        }
+    // (a row past the end re-reads the last one: no effect on the extremes, and no load under a condition)
+    for (int t = rgrp; t - rgrp < n; t += kRows * kQAbsLoads) {
+        uint4 v[kQAbsLoads];
+#pragma unroll
+        for (int u = 0; u < kQAbsLoads; ++u) v[u] = load16(base, (size_t)min(t + u * kRows, n - 1) * kRowBytes + 16 * j);
+#pragma unroll
+        for (int u = 0; u < kQAbsLoads; ++u) {
+            const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+#pragma unroll
+                for (int p = 0; p < kPairs; ++p) {
+                    const uint32_t half = (1u << (kBits * (p + 1))) - 1u, x = w[d] & (half | (half << 16));
+                    mx[p][d] = codes_max(mx[p][d], x);
+                    mn[p][d] = codes_min(mn[p][d], x);
+                }
+        }
+    }
+    uint32_t hi[kPairs], lo[kPairs];
+#pragma unroll
+    for (int p = 0; p < kPairs; ++p) {
+        hi[p] = codes_ror<true, 8>(codes_rows_quad<true>(mx[p][0], mx[p][1], mx[p][2], mx[p][3]));
+        lo[p] = codes_ror<false, 8>(codes_rows_quad<false>(mn[p][0], mn[p][1], mn[p][2], mn[p][3]));
+        if (kLanes == 4) {
+            hi[p] = codes_ror<true, 4>(hi[p]);
+            lo[p] = codes_ror<false, 4>(lo[p]);
+        }
+    }
+    // 16-lane rows 0, 1, 2, 3 own dwords 0, 2, 1, 3; the lanes that hold the same totals divide the bounds
+    // (and, 4-bit, the halves of a dword) among themselves
+    const int row = lane >> 4, d_own = ((row & 1) << 1) | (row >> 1);
+    constexpr uint32_t kCode = (1u << kBits) - 1u;
+    *is_min = (lane & 8) != 0;
+    if constexpr (kBits == 8) {
+        // code p of the halves: channels p and p + 2 of the dword's four
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const uint32_t x = (*is_min ? lo[p] : hi[p]) >> (8 * p);
+            code[p] = (int)(x & kCode);
+            code[p + 2] = (int)((x >> 16) & kCode);
+        }
+        *ch = 16 * j + 4 * d_own;
+    } else {
+        // channels p and p + 4 of the dword's eight
+        const int upper = (lane >> 2) & 1;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) code[p] = (int)(((*is_min ? lo[p] : hi[p]) >> (4 * p + 16 * upper)) & kCode);
+        *ch = 32 * j + 8 * d_own + 4 * upper;
+    }
+}
+
+// One wave per chunk, in workgroups of one wave.  A wave's work is the chain record -> codes -> fold ->
+// store: one round trip brings 4 KiB (an ordinary chunk's codes in one or two), and the vector ALU work per
+// chunk is kept to about 350 instructions (two channels per register, the lane swaps of the fold before the
+// rotations).  Measured behind the compression of 256K tokens, 8 heads, 36K chunks, half of them 4-bit
+// (201 MB of codes, partly still on their way to memory): 52 us = 3.9 TB/s (44 us read again and again);
+// with lanes of 8 channels, one code per register and two rows in flight it was 129 us.  Two loads in
+// flight 67 us, eight 65 us (padding), four waves per workgroup 61 us against 59 before the
+// compression's stores went past the caches.
 __global__ __launch_bounds__(kQAbsWaves* LEOAM_WAVE) void abstract_build_q_kernel(
     const unsigned char* __restrict__ kblob, const QChunk* __restrict__ qmeta, const int32_t* __restrict__ chunk_off,
     const int32_t* __restrict__ n_chunks, uint16_t* __restrict__ abstract, int n_ctx, int c_max, int n_kv_heads) {
     const int b = blockIdx.z, h = blockIdx.y;
-    const int wave = threadIdx.x / LEOAM_WAVE, lane = lane_id();
-    const int grp = lane >> 4, c16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEOAM_WAVE);
     const int C = min(max(n_chunks[b], 0), c_max);
     const int32_t* off = chunk_off + (size_t)b * (c_max + 1);
     const size_t bh = (size_t)b * n_kv_heads + h;
@@ -85,70 +165,23 @@ __global__ __launch_bounds__(kQAbsWaves* LEOAM_WAVE) void abstract_build_q_kerne
     for (int c = blockIdx.x * kQAbsWaves + wave; c < C; c += gridDim.x * kQAbsWaves) {
         const QChunk m = qmeta[bh * c_max + c];
         const int t0 = min(max(off[c], 0), n_ctx);
-        const int t1 = min(max(off[c + 1], t0), n_ctx);
-        const int rowb = (m.bits == 8) ? LEOAM_D : LEOAM_D / 2;
-        const unsigned char* base = kblob + m.byte_off;
-        int mx[8], mn[8];
+        const int n = min(max(off[c + 1], t0), n_ctx) - t0;
+        int code[4] = {0, 0, 0, 0}, ch = 0;
+        bool is_min = false;
+        // (an empty chunk reads nothing: its loop does not run)
+        if (m.bits == 8) code_extremes<8>(kblob + m.byte_off, n, code, &ch, &is_min);
+        else code_extremes<4>(kblob + m.byte_off, n, code, &ch, &is_min);
+        uint32_t hb[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            mx[e] = -1;
-            mn[e] = 256;
+        for (int i = 0; i < 4; ++i) {
+            // (floor(x) = -ceil(-x))
+            const double x = (double)m.scale_k * code[i] + (double)m.zero_k;
+            const uint32_t up = half_ceil_bits(is_min ? -x : x);
+            hb[i] = n <= 0 ? (is_min ? 0x7c00u : 0xfc00u)               // empty chunk: (-inf, +inf)
+                           : up ^ (is_min ? 0x8000u : 0u);
         }
-        // lane group grp walks rows grp, grp+4, ...; two rows in flight per lane
-        int t = grp;
-        const int n = t1 - t0;
-        for (; t + 4 < n; t += 8) {
-            int x0[8], x1[8];
-            load_codes_int(base + (size_t)t * rowb, m.bits, c16, x0);
-            load_codes_int(base + (size_t)(t + 4) * rowb, m.bits, c16, x1);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                mx[e] = max(mx[e], max(x0[e], x1[e]));
-                mn[e] = min(mn[e], min(x0[e], x1[e]));
-            }
-        }
-        for (; t < n; t += 4) {
-            int x0[8];
-            load_codes_int(base + (size_t)t * rowb, m.bits, c16, x0);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                mx[e] = max(mx[e], x0[e]);
-                mn[e] = min(mn[e], x0[e]);
-            }
-        }
-        // fold the four lane groups: pack (max, 255 - min) into one register per channel pair
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            int v = (mx[e] & 0x1ff) | ((mn[e] & 0x1ff) << 16);
-#pragma unroll
-            for (int msk = 16; msk < LEOAM_WAVE; msk <<= 1) {
-                const int o = __shfl_xor(v, msk, LEOAM_WAVE);
-                const int omx = (o << 23) >> 23, omn = o >> 16;             // 9-bit fields, max may be -1
-                const int vmx = (v << 23) >> 23, vmn = v >> 16;
-                v = (max(vmx, omx) & 0x1ff) | (min(vmn, omn) << 16);
-            }
-            mx[e] = (v << 23) >> 23;
-            mn[e] = v >> 16;
-        }
-        if (grp < 2) {
-            // group 0 writes kmax, group 1 writes kmin: 8 halves = 16 bytes per lane
-            uint32_t w[4];
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                uint16_t h0, h1;
-                if (n <= 0) {
-                    h0 = h1 = (grp == 0) ? 0xfc00u : 0x7c00u;               // empty chunk: (-inf, +inf)
-                } else if (grp == 0) {
-                    h0 = half_ceil_bits((double)m.scale_k * mx[e] + (double)m.zero_k);
-                    h1 = half_ceil_bits((double)m.scale_k * mx[e + 1] + (double)m.zero_k);
-                } else {
-                    h0 = half_floor_bits((double)m.scale_k * mn[e] + (double)m.zero_k);
-                    h1 = half_floor_bits((double)m.scale_k * mn[e + 1] + (double)m.zero_k);
-                }
-                w[e / 2] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            }
-            store16(Abh, (((size_t)c * 2 + grp) * LEOAM_D + 8 * c16) * 2, make_uint4(w[0], w[1], w[2], w[3]));
-        }
+        *reinterpret_cast<uint2*>(Abh + ((size_t)c * 2 + (is_min ? 1 : 0)) * LEOAM_D + ch) =
+            make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
     }
 }
 

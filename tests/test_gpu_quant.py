@@ -179,3 +179,27 @@ def test_quant_one_call_equals_separate_calls(L, oracle, n_ctx, G):
     out, lse = oracle.sparse_attention_q(c.q.cpu(), kb, vb, qm, off, sel, cnt)
     assert np.abs(one[3].cpu().numpy().astype(np.float64) - out).max() <= TOL
     assert np.abs(one[4].cpu().numpy().astype(np.float64) - lse).max() <= 1e-3
+
+
+@pytest.mark.parametrize("four", [False, True])
+def test_quant_abstract_at_load_edges(L, oracle, four):
+    """Chunk sizes around a wave-wide load (8 or 16 rows) and around the loads in flight (32 or 64), and an empty chunk."""
+    sizes = [1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 300, 0, 5]
+    off = np.cumsum([0] + sizes).astype(np.int32)[None]
+    n, c_max = int(off[0, -1]), len(sizes)
+    counts = np.asarray([c_max], np.int32)
+    g = torch.Generator().manual_seed(5)
+    K = torch.randn(1, 2, n, 128, generator=g) * torch.linspace(0.2, 3.0, n)[:, None]
+    full = [s > 0 for s in sizes]                    # the generator's store takes no empty chunk: built without, then put in
+    kb, _, qm = gen.quantize_store(K, K, np.unique(off)[None].astype(np.int32), np.asarray([sum(full)], np.int32),
+                                   np.full((1, sum(full)), four))
+    want_ab = oracle.abstract_build_q(kb, qm, np.unique(off)[None].astype(np.int32), np.asarray([sum(full)], np.int32))
+    meta = torch.zeros(1, 2, c_max, 8, dtype=qm.dtype)
+    meta[:, :, full] = qm
+    shape = L.make_shape(1, 8, 2, 128, n, c_max, 1, L.binding.Q8Q4)
+    ab = torch.full((1, 2, c_max, 2, 128), float("nan"), dtype=torch.float16, device="cuda")
+    L.kv_chunk_abstract_build(shape, kb.cuda(), torch.from_numpy(off).cuda(), torch.from_numpy(counts).cuda(), ab, qmeta=meta.cuda())
+    got = ab.cpu().to(torch.float64).numpy()
+    assert np.array_equal(got[:, :, full], want_ab)
+    empty = [not f for f in full]
+    assert np.isneginf(got[:, :, empty, 0]).all() and np.isposinf(got[:, :, empty, 1]).all()
