@@ -10,7 +10,27 @@
 namespace leoam {
 
 constexpr int kFusedWaves = kSelWaves;                 // 16
-constexpr int kFusedMergeBatch = 16;
+constexpr int kFusedMergeBatch = 16;                   // one state per lane of a 16-lane row
+
+// Online-softmax states of one (head, channel) that are folded by a lane: (m, l) of state i sits in lane i of
+// every 16-lane row (m = -inf: no such state), column(i) gives its accumulator of this lane's channel for
+// i < kStates.  Broadcasts inside the row hand the weights round: a lane reads (or loads) one (m, l) and not
+// all of them, and takes one exponential instead of sixteen.
+struct FoldedState {
+    float m = -INFINITY, l = 0.f, o = 0.f;
+    template <int kStates, typename Column> __device__ __forceinline__ void fold(float m_i, float l_i, Column&& column) {
+        float top = m_i;
+        top = fmaxf(top, dpp_f<0xB1>(top));
+        top = fmaxf(top, dpp_f<0x4E>(top));
+        top = fmaxf(top, dpp_f<0x141>(top));
+        top = fmaxf(top, dpp_f<0x140>(top));
+        const float m_new = fmaxf(m, top), c = exp2_or_zero(m, m_new), a = exp2_or_zero(m_i, m_new);
+        m = m_new;
+        l = l * c + row16_sum(a * l_i);
+        o *= c;
+        static_for<0, kStates>([&](auto i) { o = fmaf(row_bcast<decltype(i)::value>(a), column(decltype(i)::value), o); });
+    }
+};
 
 // `exchange` (two splits only, else nullptr): one 64-bit word per (b, q head, channel), zero between calls.
 // The two workgroups of a (sequence, kv head) then combine without a ticket and without waiting for
@@ -18,26 +38,27 @@ constexpr int kFusedMergeBatch = 16;
 // with ONE atomic exchange; the lane that finds the other split's pair there combines the two, in
 // split order, writes the output and puts the word back to zero.  The value travels inside the atomic
 // itself, so nothing depends on the order of separate memory operations.
-template <int G>
-__device__ __forceinline__ void fused_tail(float (*xw)[G][kPartStride], int32_t& sh_last, float* partial,
+//
+// A wave carries kHeads of the group's G heads: xw[w][j] is head j of part w / (waves per part).
+// n_splits of the launch's `stride` splits take part (partials are laid out for `stride`).
+template <int G, int kHeads>
+__device__ __forceinline__ void fused_tail(float (*xw)[kHeads][kPartStride], int32_t& sh_last, float* partial,
                                            int32_t* arrivals, float* __restrict__ out, float* __restrict__ lse,
-                                           size_t bh, int split, int n_splits,
+                                           size_t bh, int split, int n_splits, int stride,
                                            unsigned long long* exchange = nullptr) {
+    constexpr int kWaves = kFusedWaves * kHeads / G;       // waves that hold a head
     const int tid = threadIdx.x;
     // ---- fold the waves: lane (g, d) gets the split's (m, l, o[d]) ----------------
     const int g = tid >> 7, d = tid & (LEOAM_D - 1);
     const bool owner = tid < G * LEOAM_D;
-    float m = -INFINITY, l = 0.f, o = 0.f;
-    if (owner) {
-#pragma unroll
-        for (int w = 0; w < kFusedWaves; ++w) m = fmaxf(m, xw[w][g][LEOAM_D]);
-#pragma unroll
-        for (int w = 0; w < kFusedWaves; ++w) {
-            const float a = exp2_or_zero(xw[w][g][LEOAM_D], m);
-            l += a * xw[w][g][LEOAM_D + 1];
-            o += a * xw[w][g][d];
-        }
+    FoldedState state;
+    if (owner) {      // (whole waves: a head is two of them)
+        const float(*x)[kHeads][kPartStride] = xw + (g / kHeads) * kWaves;
+        const int j = g % kHeads, w = lane_id() & (kFusedMergeBatch - 1);
+        const float m_w = w < kWaves ? x[w][j][LEOAM_D] : -INFINITY, l_w = w < kWaves ? x[w][j][LEOAM_D + 1] : 0.f;
+        state.fold<kWaves>(m_w, l_w, [&](int i) { return x[i][j][d]; });
     }
+    float m = state.m, l = state.l, o = state.o;
     const size_t bj = bh * G + g;
     if (n_splits == 2 && exchange != nullptr) {
         if (!owner) return;
@@ -65,7 +86,7 @@ __device__ __forceinline__ void fused_tail(float (*xw)[G][kPartStride], int32_t&
     }
     if (n_splits > 1) {
         // publish the partial, take a ticket; the last workgroup to arrive merges
-        float* mine = partial + (bj * (size_t)n_splits + split) * kPartStride;
+        float* mine = partial + (bj * (size_t)stride + split) * kPartStride;
         if (owner) {
             __hip_atomic_store(&mine[d], o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (d == 0) {
@@ -78,51 +99,40 @@ __device__ __forceinline__ void fused_tail(float (*xw)[G][kPartStride], int32_t&
         if (tid == 0) {
             const int ticket = __hip_atomic_fetch_add(&arrivals[bh], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int is_last = ticket == n_splits - 1;
-            if (is_last) __hip_atomic_store(&arrivals[bh], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             sh_last = is_last;
         }
         __syncthreads();
         if (!sh_last || !owner) return;
-        const float* base = partial + bj * (size_t)n_splits * kPartStride;
-        m = -INFINITY;
-        l = 0.f;
-        o = 0.f;
-        // partials are fetched a batch at a time (one memory round trip each); two splits need a
-        // small batch, the many splits of a small batch of sequences a large one
+        const float* base = partial + bj * (size_t)stride * kPartStride;
+        state = FoldedState{};
+        // a batch of partials is one memory round trip: (m, l) of a split per lane, its column from each
         auto merge_batch = [&](int s0, auto width) {
             constexpr int kW = decltype(width)::value;
-            float ms[kW], ls[kW], os[kW];
+            const int own = s0 + (lane_id() & (kFusedMergeBatch - 1));
+            const bool real = own < n_splits && own < s0 + kW;
+            const unsigned long long ml = __hip_atomic_load(
+                reinterpret_cast<const unsigned long long*>(base + (size_t)min(own, n_splits - 1) * kPartStride + LEOAM_D),
+                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            float os[kW];
 #pragma unroll
-            for (int i = 0; i < kW; ++i) {
-                const float* p = base + (size_t)min(s0 + i, n_splits - 1) * kPartStride;
-                ms[i] = __hip_atomic_load(&p[LEOAM_D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ls[i] = __hip_atomic_load(&p[LEOAM_D + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                os[i] = __hip_atomic_load(&p[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (s0 + i >= n_splits) {
-                    ms[i] = -INFINITY;
-                    ls[i] = 0.f;
-                    os[i] = 0.f;
-                }
-            }
-            float mb = m;
-#pragma unroll
-            for (int i = 0; i < kW; ++i) mb = fmaxf(mb, ms[i]);
-            const float c = exp2_or_zero(m, mb);
-            o *= c;
-            l *= c;
-            m = mb;
-#pragma unroll
-            for (int i = 0; i < kW; ++i) {
-                const float a = exp2_or_zero(ms[i], m);
-                o += a * os[i];
-                l += a * ls[i];
-            }
+            for (int i = 0; i < kW; ++i)      // (past the end: the last split's, with weight 0)
+                os[i] = __hip_atomic_load(&base[(size_t)min(s0 + i, n_splits - 1) * kPartStride + d], __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+            state.fold<kW>(real ? bits_to_float((uint32_t)ml) : -INFINITY, real ? bits_to_float((uint32_t)(ml >> 32)) : 0.f,
+                           [&](int i) { return os[i]; });
         };
         if (n_splits <= 4) {
             merge_batch(0, std::integral_constant<int, 4>{});
+        } else if (n_splits <= 8) {
+            merge_batch(0, std::integral_constant<int, 8>{});
         } else {
             for (int s0 = 0; s0 < n_splits; s0 += kFusedMergeBatch) merge_batch(s0, std::integral_constant<int, kFusedMergeBatch>{});
         }
+        m = state.m;
+        l = state.l;
+        o = state.o;
+        // (behind the loads: the memory counter is in order, a store before them would be waited for)
+        if (tid == 0) __hip_atomic_store(&arrivals[bh], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!owner) return;
     out[bj * LEOAM_D + d] = (l > 0.f) ? o / l : 0.f;

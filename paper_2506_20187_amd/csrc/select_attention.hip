@@ -1,6 +1,6 @@
 // chunk_select_attention_decode: the selection (paper Sec. 4.2 / 6.1) and the
 // attention over the kept chunks (Sec. 2.1 Eq. 1, Sec. 4.1 workflow) of a decode
-// step in ONE launch, for 16-bit keys / values.
+// step in ONE launch, for keys / values stored as they are (16-bit or fp32).
 //
 // The two steps are short, dependent and latency-bound at decode batch sizes: as
 // separate launches they pay a launch gap, a round trip of the kept list through
@@ -36,17 +36,44 @@
 namespace leoam {
 
 constexpr int kFusedBlock = 128;                       // tokens a wave maps to rows at a time
-constexpr int kFusedGranule = kFusedWaves * 16;        // a split is a multiple of this many tokens
+constexpr int kFusedHeads = 4;                         // query heads a wave accumulates, at most
 constexpr int kFusedMaxSel = 2048;                     // kept chunks per (b,h) whose ranges fit the LDS tables
 constexpr int kFusedMaxSplits = 64;
 constexpr int kFusedTargetWgs = 256;                   // one workgroup per compute unit
 constexpr size_t kArrivalAlign = 256;
 
-// one 16-token tile of a wave: K operand (4 x 16 B per lane) and V rows (4 x 16 B per lane)
-struct FusedKvTile {
-    uint4 k[4];
-    uint4 v[4];
+// How a group of G query heads is laid over the sixteen waves.  A wave keeps eight accumulators per head and
+// lane, so at most four heads fit beside a tile in its 128 registers; with eight heads the waves form two
+// halves that stream the SAME tokens, four heads each (the second reader of a row finds it in the caches: the
+// chip has that bandwidth to spare, the registers it has not).
+template <int G> struct FusedPlan {
+    static constexpr int kHeads = G < kFusedHeads ? G : kFusedHeads;      // heads of a wave
+    static constexpr int kParts = G / kHeads;                             // waves that share a token stream
+    static constexpr int kStreams = kFusedWaves / kParts;
+    static constexpr int kGranule = kStreams * 16;                        // a split is a multiple of this many tokens
 };
+
+// one 16-token tile of a wave: K operand (a quarter of a row per lane: ROWB / 64 pieces of 16 bytes) and
+// V rows (four rows per lane, ROWB / 256 pieces of each)
+template <typename T> struct FusedKvTile {
+    uint4 k[Row<T>::kRowBytes / 64];
+    uint4 v[4][Row<T>::kRowBytes / 256];
+};
+
+// q . k of a tile's 16 tokens: D[token][head] += A[token][channels] B[channels][head], both operands as
+// they lie in memory.  16-bit: piece s is one step of 32 channels.  fp32: v_mfma_f32_16x16x4_f32 takes one
+// channel per lane, element e of piece s is step 4 s + e (products and sums in fp32, as on the vector ALU).
+template <typename T>
+__device__ __forceinline__ f32x4_t tile_step(const uint4& a, const uint4& b, f32x4_t c) {
+    if constexpr (T::kBytes == 2) {
+        return mfma_16x16x32<T>(a, b, c);
+    } else {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.x), bits_to_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.y), bits_to_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.z), bits_to_float(b.z), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.w), bits_to_float(b.w), c, 0, 0, 0);
+    }
+}
 
 // kGiven: the kept lists (sel_idx, sel_count) are inputs - a selection made earlier, for instance by
 // one chunk_topk_select call over all layers of a step - and the workgroup only builds its tables
@@ -58,19 +85,21 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     int32_t* __restrict__ sel_tokens, const char* __restrict__ q, const char* __restrict__ K,
     const char* __restrict__ V, float scale_log2, float* __restrict__ out, float* __restrict__ lse, float* partial,
     int32_t* arrivals, int n_splits, int c_max, int k_max, int n_kv_heads, int n_ctx, unsigned long long* exchange) {
-    constexpr int ROWB = LEOAM_D * 2;
-    constexpr int EPL = 8;
-    static_assert(G <= 4, "the fused kernel keeps 8 accumulators per head per lane");
+    constexpr int ROWB = Row<T>::kRowBytes;
+    constexpr int KP = ROWB / 64, VP = ROWB / 256;         // 16-byte pieces per lane of a K row and of a V row
+    constexpr int EPL = T::kEpl, NACC = LEOAM_D / 16;      // channels per piece, accumulators per head
+    using P = FusedPlan<G>;
+    constexpr int GH = P::kHeads;
 
     // the three phases use LDS one after the other
     union Phase {
         SelectLds sel;
         int32_t rows[kFusedWaves][kFusedBlock];
-        float xw[kFusedWaves][G][kPartStride];
+        float xw[kFusedWaves][GH][kPartStride];
     };
     __shared__ Phase ph;
     __shared__ int32_t start[kFusedMaxSel], prefix[kFusedMaxSel + 1];
-    __shared__ uint4 qs[4][LEOAM_WAVE];      // matrix-core B operand (the group's queries), same for every wave
+    __shared__ uint4 qs[P::kParts][KP][LEOAM_WAVE];      // matrix-core B operand (the group's queries)
     __shared__ int32_t sh_last;
 
     const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -80,16 +109,18 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     const int C = min(max(n_chunks[b], 0), c_max);
     const int32_t* off = chunk_off + (size_t)b * (c_max + 1);
 
-    // ---- B operand: the group's queries (column = head), zero beyond G.  Fetched by
-    // one wave while the selection runs, handed to the others through LDS.
-    uint4 qb[4];
-    if (wave == 0) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const size_t qrow = ((size_t)b * n_kv_heads * G + (size_t)h * G + min(c16, G - 1)) * ROWB;
-            qb[s] = load16(q, qrow + 64 * s + 16 * grp);
-        }
+    // ---- B operand: the group's queries (column = head), zero beyond the wave's heads.  A piece per wave,
+    // fetched while the selection runs, handed to the others through LDS.
+    static_assert(P::kParts * KP <= kFusedWaves, "a wave stages one piece");
+    const int q_part = wave / KP, q_piece = wave % KP;
+    uint4 qb = make_uint4(0, 0, 0, 0);
+    if (q_part < P::kParts) {
+        const size_t qrow = ((size_t)b * n_kv_heads * G + (size_t)h * G + q_part * GH + min(c16, GH - 1)) * ROWB;
+        qb = load16(q, qrow + 64 * q_piece + 16 * grp);
     }
+    auto stage_queries = [&] {
+        if (q_part < P::kParts) qs[q_part][q_piece][lane] = (c16 < GH) ? qb : make_uint4(0, 0, 0, 0);
+    };
 
     int cnt, total;
     if constexpr (kGiven) {
@@ -124,10 +155,7 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
         cnt = listed;
         total = (int)(uint32_t)tot;
         if (tid == 0) prefix[cnt] = total;
-        if (wave == 0) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) qs[s][lane] = (c16 < G) ? qb[s] : make_uint4(0, 0, 0, 0);
-        }
+        stage_queries();
     } else {
         // ---- selection --------------------------------------------------------------
         SelectResult<kIpt> R;
@@ -154,10 +182,7 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
                 tok += (int)R.size[i];
             }
             if (tid == 0) prefix[cnt] = total;
-            if (wave == 0) {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) qs[s][lane] = (c16 < G) ? qb[s] : make_uint4(0, 0, 0, 0);
-            }
+            stage_queries();
             if (split == 0) {
                 for (int i = cnt + tid; i < k_max; i += kSelThreads) ids[i] = -1;
                 if (tid == 0) {
@@ -171,12 +196,16 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
 
     // ---- this workgroup's range of the kept tokens, then this wave's share --------
     int per_split = (total + n_splits - 1) / n_splits;
-    per_split = ((per_split + kFusedGranule - 1) / kFusedGranule) * kFusedGranule;
+    per_split = max(1, (per_split + P::kGranule - 1) / P::kGranule) * P::kGranule;
+    // splits that hold tokens; the others (fewer tokens were kept than the launch was sized for) leave here,
+    // and the merge counts only these
+    const int n_active = max(1, (total + per_split - 1) / per_split);
+    if (split >= n_active) return;
     const int r0 = min(total, split * per_split), r1 = min(total, r0 + per_split);
-    const int per_wave = per_split / kFusedWaves;
-    const int w0 = min(r1, r0 + wave * per_wave), w1 = min(r1, w0 + per_wave);
+    const int per_wave = per_split / P::kStreams, part = P::kParts == 1 ? 0 : wave / P::kStreams;
+    const int w0 = min(r1, r0 + (wave % P::kStreams) * per_wave), w1 = min(r1, w0 + per_wave);
 
-    // uniform bases; a lane adds a 32-bit offset (n_ctx * 256 bytes stays far below 4 GiB)
+    // uniform bases; a lane adds a 32-bit offset (n_ctx rows stay below 4 GiB)
     const char* Kbh = K + bh * (size_t)n_ctx * ROWB;
     const char* Vbh = V + bh * (size_t)n_ctx * ROWB;
     const uint32_t k_lane = 16u * grp, v_lane = 16u * c16;
@@ -185,34 +214,35 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     // lanes (grp, head) carry the softmax state of `head`; every lane carries the
     // accumulators of all heads for the V rows of its group and its 8 columns
     float m_run = -INFINITY, l_run = 0.f;
-    float acc[G][EPL];
+    float acc[GH][NACC];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+    for (int g = 0; g < GH; ++g)
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
+        for (int e = 0; e < NACC; ++e) acc[g][e] = 0.f;
 
     // Loads are unconditional (a load under a condition is waited for on its own):
-    // a position past the end reads row 0, its logit is masked to -inf, its weight is 0.
-    auto fetch = [&](int t, FusedKvTile& kv) {
-        const int krow = max(my_rows[16 * t + c16], 0);
+    // a position past the end reads the block's last row (`end`), its logit is masked to -inf, its weight is 0.
+    auto fetch = [&](int t, FusedKvTile<T>& kv, int end) {
+        const int krow = my_rows[min(16 * t + c16, end)];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) kv.k[s] = load16(Kbh, (size_t)((uint32_t)krow * ROWB + k_lane + 64u * s));
+        for (int s = 0; s < KP; ++s) kv.k[s] = load16(Kbh, (size_t)((uint32_t)krow * ROWB + k_lane + 64u * s));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int vrow = max(my_rows[16 * t + 4 * grp + i], 0);
-            kv.v[i] = load16(Vbh, (size_t)((uint32_t)vrow * ROWB + v_lane));
+            const int vrow = my_rows[min(16 * t + 4 * grp + i, end)];
+#pragma unroll
+            for (int s = 0; s < VP; ++s) kv.v[i][s] = load16(Vbh, (size_t)((uint32_t)vrow * ROWB + v_lane + 256u * s));
         }
     };
     int q_lane = lane;
     auto logits = [&](const uint4* k) {
-        // the B operand is re-read from LDS for every tile: 16 registers a wave cannot spare
+        // the B operand is re-read from LDS for every tile: registers a wave cannot spare
         asm volatile("" : "+v"(q_lane));
         f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) sacc = mfma_16x16x32<T>(k[s], qs[s][q_lane], sacc);
+        for (int s = 0; s < KP; ++s) sacc = tile_step<T>(k[s], qs[part][s][q_lane], sacc);
         return sacc;
     };
-    auto accumulate = [&](f32x4_t sacc, const uint4* v, int n_valid) {
+    auto accumulate = [&](f32x4_t sacc, const uint4 (*v)[VP], int n_valid) {
         // sacc[r] = logit of token 4grp + r of the tile, head c16
         float z[4];
         float mloc = -INFINITY;
@@ -224,7 +254,7 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
         mloc = rows_max4(mloc);
         const float m_new = fmaxf(m_run, mloc);
         const float corr = exp2_or_zero(m_run, m_new);
-        const bool changed = (c16 < G) && (m_new > m_run);
+        const bool changed = (c16 < GH) && (m_new > m_run);
         m_run = m_new;
         float psum = 0.f;
 #pragma unroll
@@ -235,22 +265,23 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
         l_run = l_run * corr + psum;
         if (__ballot(changed) != 0ull) {
             // head g's correction factor sits in lane g of every row
-            static_for<0, G>([&](auto gc) {
+            static_for<0, GH>([&](auto gc) {
                 constexpr int g = decltype(gc)::value;
                 const float cg = row_bcast<g>(corr);
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) acc[g][e] *= cg;
+                for (int e = 0; e < NACC; ++e) acc[g][e] *= cg;
             });
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float x[EPL];
-            unpack<T>(v[i], x);
-            static_for<0, G>([&](auto gc) {
+            float x[NACC];
+#pragma unroll
+            for (int s = 0; s < VP; ++s) unpack<T>(v[i][s], x + s * EPL);
+            static_for<0, GH>([&](auto gc) {
                 constexpr int g = decltype(gc)::value;
                 const float p = row_bcast<g>(z[i]);
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p, x[e], acc[g][e]);
+                for (int e = 0; e < NACC; ++e) acc[g][e] = fmaf(p, x[e], acc[g][e]);
             });
         }
     };
@@ -274,7 +305,7 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
             }
 #pragma unroll
             for (int j = 0; j < PER; ++j) {
-                int p = -1;
+                int p = 0;
                 if (i0 + j < nb) {
                     const int x = blk + i0 + j;
                     while (prefix[lo + 1] <= x) ++lo;      // ends: prefix[cnt] = total > x
@@ -287,8 +318,18 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
         __builtin_amdgcn_wave_barrier();
 
         const int n_tiles = (nb + 15) >> 4, last = n_tiles - 1;
-        FusedKvTile cur, nxt;
-        fetch(0, cur);
+        if constexpr (T::kBytes == 4) {
+            // a tile is 16 KiB: one per wave keeps 256 KiB of the compute unit's loads in flight, and two
+            // do not fit the registers
+            for (int t = 0; t < n_tiles; ++t) {
+                FusedKvTile<T> cur;
+                fetch(t, cur, nb - 1);
+                accumulate(logits(cur.k), cur.v, nb - 16 * t);
+            }
+            continue;
+        }
+        FusedKvTile<T> cur, nxt;
+        fetch(0, cur, nb - 1);
         if (n_tiles == 1) {
             // a single tile (small batches spread a (b,h) over many workgroups): nothing to prefetch,
             // and the pipeline's re-reads of the last tile would triple the load instructions
@@ -297,10 +338,10 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
         }
         for (int t = 0; t < n_tiles; t += 2) {
             // (no loads under a condition: a tile index past the end re-reads the last tile)
-            fetch(min(t + 1, last), nxt);
+            fetch(min(t + 1, last), nxt, nb - 1);
             __builtin_amdgcn_sched_barrier(0);       // keep the loads ahead of the tile's arithmetic
             accumulate(logits(cur.k), cur.v, nb - 16 * t);
-            fetch(min(t + 2, last), cur);
+            fetch(min(t + 2, last), cur, nb - 1);
             __builtin_amdgcn_sched_barrier(0);
             if (t + 1 < n_tiles) accumulate(logits(nxt.k), nxt.v, nb - 16 * (t + 1));
         }
@@ -311,25 +352,27 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     // accumulator kRowOwns[r] of the quad, so all 64 lanes write to LDS
     l_run = rows_sum4(l_run, l_run, l_run, l_run);
     const int e_own = ((grp & 1) << 1) | (grp >> 1);        // rows 0,1,2,3 own accumulators 0,2,1,3
-    float folded[G][2];
+    float folded[GH][2];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < GH; ++g) {
         folded[g][0] = rows_sum4(acc[g][0], acc[g][1], acc[g][2], acc[g][3]);
         folded[g][1] = rows_sum4(acc[g][4], acc[g][5], acc[g][6], acc[g][7]);
     }
     __syncthreads();      // every wave is done with its row table: LDS becomes the exchange buffer
+    // (16-bit: a lane's eight channels are neighbours; fp32: four in each half of the row)
+    constexpr int kUpper = VP == 1 ? 4 : 16 * EPL;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < GH; ++g) {
         ph.xw[wave][g][c16 * EPL + e_own] = folded[g][0];
-        ph.xw[wave][g][c16 * EPL + 4 + e_own] = folded[g][1];
+        ph.xw[wave][g][c16 * EPL + kUpper + e_own] = folded[g][1];
     }
-    if (grp == 0 && c16 < G) {
+    if (grp == 0 && c16 < GH) {
         ph.xw[wave][c16][LEOAM_D] = m_run;
         ph.xw[wave][c16][LEOAM_D + 1] = l_run;
     }
     __syncthreads();
 
-    fused_tail<G>(ph.xw, sh_last, partial, arrivals, out, lse, bh, split, n_splits, exchange);
+    fused_tail<G, GH>(ph.xw, sh_last, partial, arrivals, out, lse, bh, split, n_active, n_splits, exchange);
 }
 
 // zero fill (arrival counters of a fresh workspace)
@@ -382,15 +425,24 @@ static inline size_t fused_part_bytes_per_split(const leoam_shape* s) {
 }
 
 bool select_attention_is_fused(const leoam_shape* s) {
-    const int g = s->n_q_heads / s->n_kv_heads;
-    // (the kernel adds 32-bit row offsets to a per-(b,h) base: n_ctx * 256 bytes must stay below 4 GiB)
-    return (s->kv_dtype == LEOAM_F16 || s->kv_dtype == LEOAM_BF16) && g <= 4 && s->k_max <= kFusedMaxSel &&
-           s->c_max <= 8 * kSelThreads && s->n_ctx < (1 << 24);
+    // (the kernel adds 32-bit row offsets to a per-(b,h) base: n_ctx rows must stay below 4 GiB)
+    return s->kv_dtype != LEOAM_Q8Q4 && s->k_max <= kFusedMaxSel && s->c_max <= 8 * kSelThreads &&
+           s->n_ctx < (s->kv_dtype == LEOAM_F32 ? 1 << 23 : 1 << 24);
+}
+// the shapes whose two-split launches merge through exchange words
+static inline bool has_exchange(const leoam_shape* s) {
+    return select_attention_is_fused(s) && s->kv_dtype != LEOAM_F32 && s->n_q_heads / s->n_kv_heads <= kFusedHeads;
 }
 
+// Tokens a split is a multiple of, and the largest useful number of splits of a (b, h): up to one workgroup
+// per compute unit (that is what workspaces are sized for).
+static inline int fused_granule(const leoam_shape* s) {
+    return (s->n_q_heads / s->n_kv_heads > kFusedHeads ? FusedPlan<8>::kGranule : FusedPlan<1>::kGranule);
+}
 static int fused_recommended_splits(const leoam_shape* s, int max_tokens) {
     if (max_tokens <= 0 || max_tokens > s->n_ctx) max_tokens = s->n_ctx;
-    const int by_tokens = (max_tokens + kFusedGranule - 1) / kFusedGranule;
+    const int granule = fused_granule(s);
+    const int by_tokens = (max_tokens + granule - 1) / granule;
     const int units = s->batch * s->n_kv_heads;
     int want = (kFusedTargetWgs + units - 1) / units;
     if (want > by_tokens) want = by_tokens;
@@ -404,7 +456,7 @@ static int fused_recommended_splits(const leoam_shape* s, int max_tokens) {
 // (b, h), i.e. between half a workgroup and one workgroup per compute unit.
 static inline size_t exchange_bytes(const leoam_shape* s) {
     const long long units = (long long)s->batch * s->n_kv_heads;
-    if (!select_attention_is_fused(s) || (kFusedTargetWgs + units - 1) / units != 2) return 0;
+    if (!has_exchange(s) || (kFusedTargetWgs + units - 1) / units != 2) return 0;
     return (size_t)s->batch * s->n_q_heads * LEOAM_D * sizeof(unsigned long long);
 }
 
@@ -431,7 +483,7 @@ size_t select_attention_workspace_bytes(const leoam_shape* s, int max_tokens, bo
 size_t select_attention_counter_bytes(const leoam_shape* s, bool with_exchange) { return control_bytes(s, with_exchange); }
 
 size_t select_attention_min_workspace_bytes(const leoam_shape* s, bool with_exchange) {
-    const bool one_launch = (select_attention_is_fused(s) || select_attention_q_is_fused(s)) && !stream_ordered_merge_wanted();
+    const bool one_launch = (has_exchange(s) || select_attention_q_is_fused(s)) && !stream_ordered_merge_wanted();
     return control_bytes(s, with_exchange) + (one_launch ? 0 : attention_min_workspace_bytes(s));
 }
 
@@ -473,9 +525,35 @@ static hipError_t fused_by_group(const leoam_shape* s, const float* score, const
     switch (s->n_q_heads / s->n_kv_heads) {
     case 1: return LEOAM_FG(1);
     case 2: return LEOAM_FG(2);
-    default: return LEOAM_FG(4);
+    case 4: return LEOAM_FG(4);
+    default: return LEOAM_FG(8);
     }
 #undef LEOAM_FG
+}
+
+// Splits of a one-launch call, at most `cap`: the number for which the launch is estimated to take the least
+// time.  Workgroups run in rounds of one per compute unit; a round costs its fixed part (selection and fold
+// about 7 us, publishing and merging a split about 3) and its streaming at 40 GB/s per workgroup or 6.2 TB/s
+// for the chip, whichever is slower.  With one split more than fills the chip (192 (b,h), two splits: 384
+// workgroups) the second round costs more than the shorter splits save: 35 us against 24 at 1024 tokens.
+static int fused_pick_splits(int units, int tokens, int token_bytes, int granule, int cap) {
+    int best = 1;
+    double best_us = 0.0;
+    for (int s = 1; s <= cap; ++s) {
+        const int per_split = ((tokens + s - 1) / s + granule - 1) / granule * granule;
+        const double bytes = (double)per_split * token_bytes, fixed = s == 1 ? 7.0 : 10.0;
+        auto round_us = [&](long long wgs) {
+            const double one = bytes / 40e3, all = (double)wgs * bytes / 6.2e6;
+            return fixed + (one > all ? one : all);
+        };
+        const long long wgs = (long long)units * s, rounds = wgs / kFusedTargetWgs, rest = wgs % kFusedTargetWgs;
+        const double us = (double)rounds * round_us(kFusedTargetWgs) + (rest ? round_us(rest) : 0.0);
+        if (s == 1 || us < best_us) {
+            best = s;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, const void* q, const void* K,
@@ -503,9 +581,11 @@ hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, c
     if (select_attention_q_is_fused(s)) {
         // the compressed store's one-launch kernel (select_attention_q.hip)
         size_t n = body_bytes / fused_part_bytes_per_split(s);
-        const size_t cap = (size_t)fused_q_recommended_splits(s, token_budget > 0 ? token_budget : s->n_ctx);
+        const int tokens = token_budget > 0 && token_budget < s->n_ctx ? token_budget : s->n_ctx;
+        const size_t cap = (size_t)fused_q_recommended_splits(s, tokens);
         if (n > cap) n = cap;
         if (n < 1) n = 1;
+        n = (size_t)fused_pick_splits(s->batch * s->n_kv_heads, tokens, 2 * LEOAM_D, kFusedWaves * 16, (int)n);
         return select_attention_q_dispatch(s, score, q, K, V, qmeta, chunk_off, n_chunks, max_chunks, token_budget, scale,
                                            sel_idx, sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace,
                                            (int)n, stream);
@@ -520,10 +600,16 @@ hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, c
                                   body_bytes, (int32_t*)workspace, stream);
     }
     size_t n = body_bytes / fused_part_bytes_per_split(s);
-    const size_t cap = (size_t)fused_recommended_splits(s, token_budget > 0 ? token_budget : s->n_ctx);
+    const int tokens = token_budget > 0 && token_budget < s->n_ctx ? token_budget : s->n_ctx;
+    const size_t cap = (size_t)fused_recommended_splits(s, tokens);
     if (n > cap) n = cap;
     if (n < 1) n = 1;      // a single split needs no partials
-    const int n_splits = (int)n;
+    const int row_bytes = LEOAM_D * (s->kv_dtype == LEOAM_F32 ? 4 : 2);
+    const int n_splits = fused_pick_splits(s->batch * s->n_kv_heads, tokens, 2 * row_bytes, fused_granule(s), (int)n);
+    if (s->kv_dtype == LEOAM_F32)
+        return fused_by_group<F32>(s, score, q, K, V, chunk_off, n_chunks, max_chunks, token_budget, scale, sel_idx,
+                                   sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace, n_splits, exchange,
+                                   stream);
     if (s->kv_dtype == LEOAM_F16)
         return fused_by_group<F16>(s, score, q, K, V, chunk_off, n_chunks, max_chunks, token_budget, scale, sel_idx,
                                    sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace, n_splits, exchange,

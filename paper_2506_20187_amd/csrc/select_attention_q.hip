@@ -151,7 +151,10 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_q_kernel(
 
     // ---- this workgroup's range of the kept tokens, then this wave's share --------
     int per_split = (listed + n_splits - 1) / n_splits;
-    per_split = ((per_split + kFusedQGranule - 1) / kFusedQGranule) * kFusedQGranule;
+    per_split = max(1, (per_split + kFusedQGranule - 1) / kFusedQGranule) * kFusedQGranule;
+    // splits that hold tokens; the others leave here, and the merge counts only these
+    const int n_active = max(1, (listed + per_split - 1) / per_split);
+    if (split >= n_active) return;
     const int r0 = min(listed, split * per_split), r1 = min(listed, r0 + per_split);
     const int per_wave = per_split / kFusedWaves;
     const int w0 = min(r1, r0 + wave * per_wave), w1 = min(r1, w0 + per_wave);
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_q_kernel(
         ph.xw[wave][c16][LEOAM_D + 1] = l_run;
     }
     __syncthreads();
-    fused_tail<G>(ph.xw, sh_last, partial, arrivals, out, lse, bh, split, n_splits);
+    fused_tail<G, G>(ph.xw, sh_last, partial, arrivals, out, lse, bh, split, n_active, n_splits);
 }
 
 bool select_attention_q_is_fused(const leoam_shape* s) {

@@ -616,7 +616,7 @@ def gpu_select_attend(L, dtype, score, q, K, V, packed, counts, max_chunks, budg
                                        ("bf16", 2, 300), ("bf16", 1, 40), ("f16", 4, 2047), ("bf16", 4, 4500), ("bf16", 4, 7000),
                                        ("bf16", 8, 900), ("f16", 8, 3000), ("bf16", 8, 5000), ("f32", 2, 900),
                                        ("f32", 4, 1300)])
-                                       # (the last five: shapes that take two launches)
+                                       # (the last five: eight heads, fp32)
 def test_select_attention_one_call(L, oracle, dtype, G, C):
     rng = np.random.default_rng(1000 + C + G)
     B, Hkv, D = 2, 2, 128
@@ -669,7 +669,7 @@ def test_select_attention_one_call(L, oracle, dtype, G, C):
 
 @pytest.mark.parametrize("dtype,G,C", [("bf16", 4, 700), ("bf16", 4, 3000), ("f16", 1, 1500), ("f16", 2, 2047), ("bf16", 2, 40),
                                        ("bf16", 8, 900), ("f32", 2, 900)])
-                                       # (the last two: shapes that take the separate attention kernels)
+                                       # (the last two: eight heads, fp32)
 def test_one_call_with_a_given_selection(L, oracle, dtype, G, C):
     """chunk_select_attention_decode with score_ub = NULL: the kept lists are inputs (unsorted, with ids out of
     range and an empty list among them) and the call only attends; against the oracle, for every number of
@@ -741,6 +741,28 @@ def test_one_call_with_a_given_selection(L, oracle, dtype, G, C):
             assert np.array_equal(got, first[0]) and np.array_equal(got_lse, first[1])
         assert int(ws[:head].to(torch.int32).sum()) == 0           # counters are back at zero
     assert torch.equal(dsel, dev(sel)) and torch.equal(dcnt, dev(cnt)) and int(tok.min()) == -7      # inputs untouched
+
+
+@pytest.mark.parametrize("dtype,G", [("f32", 1), ("f32", 4), ("f32", 8), ("bf16", 8), ("bf16", 4), ("f16", 1)])
+def test_one_call_token_count_edges(L, oracle, dtype, G):
+    """Kept totals at the edges of a tile (16), of a split (128 / 256) and of a wave's row table, both with splits sized for
+    the tokens (budget) and with splits sized for the whole context of which few hold tokens (chunk limit)."""
+    rng = np.random.default_rng(31 + G)
+    B, Hkv, D, N = 1, 3, 128, 2300
+    packed, counts, c_max = gen.pack_boundaries([np.arange(N + 1, dtype=np.int32)], N)      # chunks of one token
+    K = torch.from_numpy(rng.standard_normal((B, Hkv, N, D)).astype(np.float32)).to(TDT[dtype])
+    V = torch.from_numpy(rng.standard_normal((B, Hkv, N, D)).astype(np.float32)).to(TDT[dtype])
+    q = torch.from_numpy(rng.standard_normal((B, Hkv * G, D)).astype(np.float32) * 1.5).to(TDT[dtype])
+    score = (rng.standard_normal((B, Hkv, c_max)) * 20).astype(np.float32)
+    for kept in (1, 15, 16, 17, 127, 128, 129, 255, 256, 257, 513, 2047, 2048):
+        want_sel, want_cnt, want_tok = oracle.topk_select(score, packed, counts, 0, kept, 2048)
+        want_out, want_lse = oracle.sparse_attention(q, K, V, packed, want_sel, want_cnt)
+        for max_chunks, budget, n_splits in ((0, kept, None), (kept, 0, None), (kept, 0, 1)):
+            sel, cnt, tok, out, lse, _ = gpu_select_attend(L, dtype, score, q, K, V, packed, counts, max_chunks, budget, 2048,
+                                                           n_splits=n_splits)
+            assert np.array_equal(sel, want_sel) and np.array_equal(cnt, want_cnt) and np.array_equal(tok, want_tok)
+            assert np.abs(out - want_out).max() <= TOL[dtype], f"kept={kept} max_chunks={max_chunks}"
+            assert np.abs(lse - want_lse).max() <= 1e-4
 
 
 def test_stream_ordered_merge_switch(L, tmp_path):
