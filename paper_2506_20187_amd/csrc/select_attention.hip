@@ -60,20 +60,13 @@ template <typename T> struct FusedKvTile {
     uint4 v[4][Row<T>::kRowBytes / 256];
 };
 
-// q . k of a tile's 16 tokens: D[token][head] += A[token][channels] B[channels][head], both operands as
-// they lie in memory.  16-bit: piece s is one step of 32 channels.  fp32: v_mfma_f32_16x16x4_f32 takes one
-// channel per lane, element e of piece s is step 4 s + e (products and sums in fp32, as on the vector ALU).
-template <typename T>
-__device__ __forceinline__ f32x4_t tile_step(const uint4& a, const uint4& b, f32x4_t c) {
-    if constexpr (T::kBytes == 2) {
-        return mfma_16x16x32<T>(a, b, c);
-    } else {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.x), bits_to_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.y), bits_to_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.z), bits_to_float(b.z), c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(bits_to_float(a.w), bits_to_float(b.w), c, 0, 0, 0);
-    }
-}
+// q . k of a tile's 16 tokens on the matrix cores.  16-bit: v_mfma_f32_16x16x32, token = row, head = column,
+// piece s of the K operand is one step.  fp32: v_mfma_f64_4x4x4 (as in chunk_score.hip: four blocks of four
+// tokens, every block carries the queries), element e of piece s is step 4 s + e, products exact and sums in
+// double.  (v_mfma_f32_16x16x4_f32 was as fast, but its sums ended up to three times further from a 64-bit
+// reference than the vector ALU's, 1.2 times when summed pairwise.)
+template <typename T> struct QueryStep { using Type = uint4; static constexpr int kPerPiece = 1; };
+template <> struct QueryStep<F32> { using Type = double; static constexpr int kPerPiece = 4; };
 
 // kGiven: the kept lists (sel_idx, sel_count) are inputs - a selection made earlier, for instance by
 // one chunk_topk_select call over all layers of a step - and the workgroup only builds its tables
@@ -99,7 +92,8 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     };
     __shared__ Phase ph;
     __shared__ int32_t start[kFusedMaxSel], prefix[kFusedMaxSel + 1];
-    __shared__ uint4 qs[P::kParts][KP][LEOAM_WAVE];      // matrix-core B operand (the group's queries)
+    using QStep = QueryStep<T>;
+    __shared__ typename QStep::Type qs[P::kParts][KP * QStep::kPerPiece][LEOAM_WAVE];      // the group's queries as matrix-core operand
     __shared__ int32_t sh_last;
 
     const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -109,17 +103,25 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     const int C = min(max(n_chunks[b], 0), c_max);
     const int32_t* off = chunk_off + (size_t)b * (c_max + 1);
 
-    // ---- B operand: the group's queries (column = head), zero beyond the wave's heads.  A piece per wave,
+    // ---- the group's queries as the matrix cores take them, zero beyond the wave's heads.  A piece per wave,
     // fetched while the selection runs, handed to the others through LDS.
     static_assert(P::kParts * KP <= kFusedWaves, "a wave stages one piece");
-    const int q_part = wave / KP, q_piece = wave % KP;
+    const int q_part = wave / KP, q_piece = wave % KP, q_head = T::kBytes == 2 ? c16 : (lane & 3);
     uint4 qb = make_uint4(0, 0, 0, 0);
     if (q_part < P::kParts) {
-        const size_t qrow = ((size_t)b * n_kv_heads * G + (size_t)h * G + q_part * GH + min(c16, GH - 1)) * ROWB;
+        const size_t qrow = ((size_t)b * n_kv_heads * G + (size_t)h * G + q_part * GH + min(q_head, GH - 1)) * ROWB;
         qb = load16(q, qrow + 64 * q_piece + 16 * grp);
     }
     auto stage_queries = [&] {
-        if (q_part < P::kParts) qs[q_part][q_piece][lane] = (c16 < GH) ? qb : make_uint4(0, 0, 0, 0);
+        if (q_part >= P::kParts) return;
+        if constexpr (T::kBytes == 2) {
+            qs[q_part][q_piece][lane] = (q_head < GH) ? qb : make_uint4(0, 0, 0, 0);
+        } else {
+            float x[EPL];
+            unpack<T>(qb, x);
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) qs[q_part][EPL * q_piece + e][lane] = (q_head < GH) ? (double)x[e] : 0.0;
+        }
     };
 
     int cnt, total;
@@ -235,20 +237,37 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     };
     int q_lane = lane;
     auto logits = [&](const uint4* k) {
-        // the B operand is re-read from LDS for every tile: registers a wave cannot spare
+        // the queries are re-read from LDS for every tile: registers a wave cannot spare
         asm volatile("" : "+v"(q_lane));
         f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (T::kBytes == 2) {
 #pragma unroll
-        for (int s = 0; s < KP; ++s) sacc = tile_step<T>(k[s], qs[part][s][q_lane], sacc);
-        return sacc;
+            for (int s = 0; s < KP; ++s) sacc = mfma_16x16x32<T>(k[s], qs[part][s][q_lane], sacc);
+            return sacc * scale_log2;
+        } else {
+            double sum[2] = {0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < KP; ++s) {
+                float x[EPL];
+                unpack<T>(k[s], x);
+#pragma unroll
+                for (int e = 0; e < EPL; ++e)
+                    sum[e & 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(qs[part][EPL * s + e][q_lane], (double)x[e], sum[e & 1], 0, 0, 0);
+            }
+            // lane 16 * head + token -> token 4 grp + r of head c16 (columns beyond the heads repeat the last)
+            const float dot = (float)((sum[0] + sum[1]) * (double)scale_log2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sacc[r] = __shfl(dot, 16 * min(c16, 3) + 4 * grp + r, LEOAM_WAVE);
+            return sacc;
+        }
     };
     auto accumulate = [&](f32x4_t sacc, const uint4 (*v)[VP], int n_valid) {
-        // sacc[r] = logit of token 4grp + r of the tile, head c16
+        // sacc[r] = logit (log2 domain) of token 4grp + r of the tile, head c16
         float z[4];
         float mloc = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            z[r] = (4 * grp + r < n_valid) ? sacc[r] * scale_log2 : -INFINITY;
+            z[r] = (4 * grp + r < n_valid) ? sacc[r] : -INFINITY;
             mloc = fmaxf(mloc, z[r]);
         }
         mloc = rows_max4(mloc);
