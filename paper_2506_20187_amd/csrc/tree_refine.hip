@@ -36,7 +36,7 @@
 // cores (v_mfma_f64_4x4x4 as in chunk_score.hip: the sixteen B rows are the
 // tokens' key rows, every A block carries the queries), the rows of several
 // such groups in flight; the initial chunks are evaluated eight at a time the
-// same way, with both bounds (B rows 0-7 their kmax rows, rows 8-15 their kmin
+// same way (many of them: in a launch of their own that fills the chip), with both bounds (B rows 0-7 their kmax rows, rows 8-15 their kmin
 // rows).  To bring the single tokens together the split nodes of a round are
 // listed in two classes (two-token nodes from the front of the task list, the
 // others from its back).  The evaluation phase dominates: its first rounds are
@@ -388,19 +388,85 @@ __device__ __forceinline__ void tree_nodes8(const uint4 (*v)[Row<T>::kRowBytes /
     *L = (float)rows_extreme4_d<true>(real ? lb : -INFINITY) + 0.0f;
 }
 
+// Wave i converts the 16-byte pieces i of a group's queries: lane (head, block, channel quarter).
+template <typename T> __device__ __forceinline__ void tree_a_operands(const char* q_group, int i, TreeMfmaLds& A, int G) {
+    constexpr int EPL = T::kEpl;
+    const int lane = lane_id(), a_head = lane & 3, kq = lane >> 4;
+    const bool a_min = ((lane >> 2) & 3) >= 2;
+    float x[EPL];
+    unpack<T>(load16(q_group, (size_t)min(a_head, G - 1) * Row<T>::kRowBytes + 64 * i + 16 * kq), x);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        const float xe = (a_head < G) ? x[e] : 0.f;
+        const float pos = fmaxf(xe, 0.f), neg = fminf(xe, 0.f);
+        A.qa[i * EPL + e][lane] = (double)(a_min ? neg : pos);
+        A.qb[i * EPL + e][lane] = (double)(a_min ? pos : neg);
+    }
+}
+
+// The initial chunks c0 ... of a wave, eight per pass, kLeafPasses<T> passes in flight (16 loads per lane): lane
+// (r, kq) reads its pieces of row 2 c + (r >> 3) of chunk c = c0 + 8 p + (r & 7) - the chunk's kmax or its kmin row.
+template <typename T> constexpr int kLeafPasses = 16 / (Row<T>::kRowBytes / 64);
+template <typename T>
+__device__ __forceinline__ void tree_fetch_leaves(const char* Abh, int c0, int m0, uint4 (*v)[1][Row<T>::kRowBytes / 64]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int p = 0; p < kLeafPasses<T>; ++p) {
+        const int c = min(c0 + 8 * p + (lane & 7), m0 - 1);
+        tree_fetch_node<T, 1>(Abh + ((size_t)2 * c + ((lane >> 3) & 1)) * Row<T>::kRowBytes, 1, v[p]);
+    }
+}
+template <typename T>
+__device__ __forceinline__ void tree_store_leaves(const uint4 (*v)[1][Row<T>::kRowBytes / 64], const TreeMfmaLds& A, int G, int c0,
+                                                  int m0, int chunk_size, int n_ctx, TreeNode* cur) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int p = 0; p < kLeafPasses<T>; ++p) {
+        const int c = c0 + 8 * p + lane;
+        TreeNode nd;
+        tree_nodes8<T, 1>(v[p], A, G, &nd.U, &nd.L);
+        if (lane < 8 && c < m0) {
+            nd.start = c * chunk_size;
+            nd.size = min(chunk_size, n_ctx - c * chunk_size);
+            cur[c] = nd;
+        }
+    }
+}
+
+// The initial chunks of every (sequence, kv head) in a launch of their own: 512 B of abstract per chunk (16-bit keys),
+// read by the whole chip instead of one workgroup per head, whose passes are a chain of round trips.
+constexpr int kLeafThreads = 512, kLeafWaves = kLeafThreads / LEOAM_WAVE;
+template <typename T>
+__global__ __launch_bounds__(kLeafThreads) void tree_leaves_kernel(const char* __restrict__ q, const char* __restrict__ abstract,
+                                                                   int chunk_size, int node_cap, TreeNode* __restrict__ nodes,
+                                                                   int n_ctx, int c_max, int n_kv_heads, int G) {
+    constexpr int ROWB = Row<T>::kRowBytes;
+    constexpr int NLOAD = ROWB / 64;
+    static_assert(kLeafWaves >= NLOAD, "a wave converts one piece of the queries");
+    __shared__ TreeMfmaLds A;
+    const size_t bh = (size_t)blockIdx.z * n_kv_heads + blockIdx.y;
+    const int wave = threadIdx.x / LEOAM_WAVE, m0 = (n_ctx + chunk_size - 1) / chunk_size;
+    const int c0 = (blockIdx.x * kLeafWaves + wave) * 8 * kLeafPasses<T>;
+    uint4 v[kLeafPasses<T>][1][NLOAD];
+    tree_fetch_leaves<T>(abstract + bh * (size_t)c_max * 2 * ROWB, c0, m0, v);       // (past the end: the last chunk again)
+    if (wave < NLOAD) tree_a_operands<T>(q + bh * G * ROWB, wave, A, G);
+    __syncthreads();
+    tree_store_leaves<T>(v, A, G, c0, m0, chunk_size, n_ctx, nodes + bh * (size_t)node_cap);
+}
+
 template <typename T>
 __global__ __launch_bounds__(kTreeThreads) void tree_refine_kernel(
     const char* __restrict__ q, const char* __restrict__ K, const char* __restrict__ abstract, int chunk_size,
     int k_tokens, int max_rounds, int node_cap, int32_t* __restrict__ ref_off, float* __restrict__ ref_score,
     int32_t* __restrict__ ref_count, int32_t* __restrict__ ref_evals, int32_t* __restrict__ ref_status,
-    TreeNode* nodes_a, TreeNode* nodes_b, TreeTask* task_buf, int n_ctx, int c_max, int n_kv_heads, int G) {
+    TreeNode* nodes_a, TreeNode* nodes_b, TreeTask* task_buf, int n_ctx, int c_max, int n_kv_heads, int G, bool leaves_done) {
     constexpr int ROWB = Row<T>::kRowBytes;
     constexpr int EPL = T::kEpl;
     __shared__ TreeLds S;
     __shared__ TreeMfmaLds A;
     constexpr int NLOAD = ROWB / 64;
     constexpr int kTokenPasses = 8 / NLOAD;        // groups of sixteen tokens a wave keeps in flight (8 loads per lane)
-    constexpr int kNodePasses = 16 / NLOAD;        // groups of eight one-row nodes in flight (16 loads per lane)
+    constexpr int kNodePasses = kLeafPasses<T>;
     const bool mfma = G <= 4;
 
     const int h = blockIdx.x, b = blockIdx.y;
@@ -430,44 +496,15 @@ __global__ __launch_bounds__(kTreeThreads) void tree_refine_kernel(
         }
     }
     for (int i = tid; i < 256; i += kTreeThreads) S.hist[i] = 0;
-    if (mfma && wave < NLOAD) {
-        // wave i converts the 16-byte pieces i of the queries: lane (head, block, channel quarter)
-        const int a_head = lane & 3, kq = lane >> 4, i = wave;
-        const bool a_min = ((lane >> 2) & 3) >= 2;
-        float x[EPL];
-        unpack<T>(load16(q, ((size_t)b * n_kv_heads * G + (size_t)h * G + min(a_head, G - 1)) * ROWB + 64 * i + 16 * kq), x);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-            const float xe = (a_head < G) ? x[e] : 0.f;
-            const float pos = fmaxf(xe, 0.f), neg = fminf(xe, 0.f);
-            A.qa[i * EPL + e][lane] = (double)(a_min ? neg : pos);
-            A.qb[i * EPL + e][lane] = (double)(a_min ? pos : neg);
-        }
-    }
+    if (mfma && wave < NLOAD) tree_a_operands<T>(q + ((size_t)b * n_kv_heads + h) * G * ROWB, wave, A, G);
     __syncthreads();
 
     // ---- initial chunks: bounds from the abstract rows (kmax row, kmin row) ----------
     if (mfma) {
-        // eight chunks per wave and pass, kNodePasses passes in flight: lane (r, kq) reads its pieces of
-        // row 2 c + (r >> 3) of chunk c = c0 + 8 p + (r & 7) - the chunk's kmax row or its kmin row
-        for (int c0 = wave * 8 * kNodePasses; c0 < m0; c0 += kTreeWaves * 8 * kNodePasses) {
+        for (int c0 = leaves_done ? m0 : wave * 8 * kNodePasses; c0 < m0; c0 += kTreeWaves * 8 * kNodePasses) {
             uint4 v[kNodePasses][1][NLOAD];
-#pragma unroll
-            for (int p = 0; p < kNodePasses; ++p) {
-                const int c = min(c0 + 8 * p + (lane & 7), m0 - 1);
-                tree_fetch_node<T, 1>(Abh + ((size_t)2 * c + ((lane >> 3) & 1)) * ROWB, 1, v[p]);
-            }
-#pragma unroll
-            for (int p = 0; p < kNodePasses; ++p) {
-                const int c = c0 + 8 * p + lane;
-                TreeNode nd;
-                tree_nodes8<T, 1>(v[p], A, G, &nd.U, &nd.L);
-                if (lane < 8 && c < m0) {
-                    nd.start = c * chunk_size;
-                    nd.size = min(chunk_size, n_ctx - c * chunk_size);
-                    cur[c] = nd;
-                }
-            }
+            tree_fetch_leaves<T>(Abh, c0, m0, v);
+            tree_store_leaves<T>(v, A, G, c0, m0, chunk_size, n_ctx, cur);
         }
     } else
     for (int c0 = wave * (LEOAM_WAVE / LPR); c0 < m0; c0 += kGroups) {      // uniform over the wave
@@ -833,14 +870,25 @@ hipError_t tree_refine_dispatch(const leoam_shape* s, const void* q, const void*
     TreeTask* task = (TreeTask*)(b + units * (size_t)node_cap);
     dim3 grid(s->n_kv_heads, s->batch), block(kTreeThreads);
     const int G = s->n_q_heads / s->n_kv_heads;
+    // The initial chunks get their own launch once the refining workgroup would need more than one pass over them
+    // (512 chunks of 16-bit keys, 256 of fp32); up to there its one pass costs no more than a launch.  Measured for the
+    // whole call and the attention after it, bf16: 2048 chunks, 8 heads 629 -> 588 us and 128 heads 786 -> 767 us;
+    // 1024 chunks, 32 heads 415 -> 400 us.
+    const int m0 = (s->n_ctx + chunk_size - 1) / chunk_size;
 #define LEOAM_TREE(TT)                                                                                           \
+    const int pass = 8 * kLeafPasses<TT>;                                                                        \
+    const bool apart = G <= 4 && m0 > kTreeWaves * pass;                                                         \
+    if (apart)                                                                                                   \
+        hipLaunchKernelGGL(tree_leaves_kernel<TT>, dim3((m0 + kLeafWaves * pass - 1) / (kLeafWaves * pass),       \
+                           s->n_kv_heads, s->batch), dim3(kLeafThreads), 0, stream, (const char*)q,               \
+                           (const char*)abstract, chunk_size, node_cap, a, s->n_ctx, s->c_max, s->n_kv_heads, G); \
     hipLaunchKernelGGL(tree_refine_kernel<TT>, grid, block, 0, stream, (const char*)q, (const char*)K,            \
                        (const char*)abstract, chunk_size, k_tokens, max_rounds, node_cap, ref_off, ref_score,    \
-                       ref_count, ref_evals, ref_status, a, b, task, s->n_ctx, s->c_max, s->n_kv_heads, G)
+                       ref_count, ref_evals, ref_status, a, b, task, s->n_ctx, s->c_max, s->n_kv_heads, G, apart)
     switch (s->kv_dtype) {
-    case LEOAM_F32: LEOAM_TREE(F32); break;
-    case LEOAM_F16: LEOAM_TREE(F16); break;
-    default: LEOAM_TREE(BF16); break;
+    case LEOAM_F32: { LEOAM_TREE(F32); break; }
+    case LEOAM_F16: { LEOAM_TREE(F16); break; }
+    default: { LEOAM_TREE(BF16); break; }
     }
 #undef LEOAM_TREE
     return hipGetLastError();

@@ -849,6 +849,19 @@ def test_tree_refine_exact(L, oracle, dtype, G, N, cs):
         check_tree(L, oracle, dtype, q, K, cs, max(1, k), rounds, cap)
 
 
+@pytest.mark.parametrize("dtype,m0", [("f32", 256), ("f32", 257), ("f32", 383), ("bf16", 512), ("bf16", 513), ("f16", 767), ("bf16", 1025)])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_tree_refine_initial_chunks_in_their_own_launch(L, oracle, dtype, m0, G):
+    """Around the number of initial chunks from which they are evaluated apart, and around that launch's workgroups; a
+    table with room for more chunks than there are."""
+    g = torch.Generator().manual_seed(m0 + G)
+    N = 4 * m0 - 3                                            # the last chunk is a single token
+    K = torch.randn(2, 2, N, 128, generator=g).to(TDT[dtype])
+    q = torch.randn(2, 2 * G, 128, generator=g).to(TDT[dtype])
+    check_tree(L, oracle, dtype, q, K, 4, 37, 0, m0)
+    check_tree(L, oracle, dtype, q, K, 4, 300, 2, N)
+
+
 @pytest.mark.parametrize("seed", list(range(16)))
 def test_tree_refine_random_shapes(L, oracle, seed):
     """Shapes and data drawn at random (seeded): dtype, group size, ragged context, initial chunk size, k, round limit,
