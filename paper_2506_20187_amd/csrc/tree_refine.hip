@@ -434,7 +434,8 @@ __device__ __forceinline__ void tree_store_leaves(const uint4 (*v)[1][Row<T>::kR
 }
 
 // The initial chunks of every (sequence, kv head) in a launch of their own: 512 B of abstract per chunk (16-bit keys),
-// read by the whole chip instead of one workgroup per head, whose passes are a chain of round trips.
+// read by the whole chip instead of one workgroup per head, whose passes are a chain of round trips
+// (128 heads x 2048 chunks, bf16: 36 us here for 134 MB against 58 us in the refining workgroups).
 constexpr int kLeafThreads = 512, kLeafWaves = kLeafThreads / LEOAM_WAVE;
 template <typename T>
 __global__ __launch_bounds__(kLeafThreads) void tree_leaves_kernel(const char* __restrict__ q, const char* __restrict__ abstract,
