@@ -550,29 +550,20 @@ static hipError_t fused_by_group(const leoam_shape* s, const float* score, const
 #undef LEOAM_FG
 }
 
-// Splits of a one-launch call, at most `cap`: the number for which the launch is estimated to take the least
-// time.  Workgroups run in rounds of one per compute unit; a round costs its fixed part (selection and fold
-// about 7 us, publishing and merging a split about 3) and its streaming at 40 GB/s per workgroup or 6.2 TB/s
-// for the chip, whichever is slower.  With one split more than fills the chip (192 (b,h), two splits: 384
-// workgroups) the second round costs more than the shorter splits save: 35 us against 24 at 1024 tokens.
-static int fused_pick_splits(int units, int tokens, int token_bytes, int granule, int cap) {
-    int best = 1;
-    double best_us = 0.0;
-    for (int s = 1; s <= cap; ++s) {
-        const int per_split = ((tokens + s - 1) / s + granule - 1) / granule * granule;
-        const double bytes = (double)per_split * token_bytes, fixed = s == 1 ? 7.0 : 10.0;
-        auto round_us = [&](long long wgs) {
-            const double one = bytes / 40e3, all = (double)wgs * bytes / 6.2e6;
-            return fixed + (one > all ? one : all);
-        };
-        const long long wgs = (long long)units * s, rounds = wgs / kFusedTargetWgs, rest = wgs % kFusedTargetWgs;
-        const double us = (double)rounds * round_us(kFusedTargetWgs) + (rest ? round_us(rest) : 0.0);
-        if (s == 1 || us < best_us) {
-            best = s;
-            best_us = us;
-        }
-    }
-    return best;
+// Splits of a one-launch call, at most `cap` (what the workspace holds): as many workgroups as run at once, one per
+// compute unit, each with an equal share of the tokens in granules; splits that this leaves without a share are not
+// launched.  A launch of one round takes as long as its longest share, so within a round shorter shares pay for the
+// merge of the splits, and a second round costs more than it saves.  Microseconds with 1 / 2 / 3 splits:
+// bf16, four heads per group, 128 (b,h), 1024 tokens 23.2 / 20.2 / 31.9; 96 (b,h), 512 tokens
+// 15.3 / 13.2 / -; 192 (b,h), 1024 tokens 26.8 / 35.4 / 37.1; compressed store, 128 (b,h), 2048 tokens
+// 49.2 / 34.8 / 59.6.  Over 4 to 256 (b,h), 256 to 8192 tokens, every type and 1 to 8 heads per group, the count taken
+// here is 0.4 % off the best one on average and 12 % at most (144 (b,h), fp32 and the compressed store: three splits).
+static int fused_pick_splits(int units, int tokens, int granule, int cap) {
+    int n = kFusedTargetWgs / units;
+    if (n > cap) n = cap;
+    if (n < 1) n = 1;
+    const int per_split = ((tokens + n - 1) / n + granule - 1) / granule * granule;
+    return (tokens + per_split - 1) / per_split;
 }
 
 hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, const void* q, const void* K,
@@ -604,7 +595,7 @@ hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, c
         const size_t cap = (size_t)fused_q_recommended_splits(s, tokens);
         if (n > cap) n = cap;
         if (n < 1) n = 1;
-        n = (size_t)fused_pick_splits(s->batch * s->n_kv_heads, tokens, 2 * LEOAM_D, kFusedWaves * 16, (int)n);
+        n = (size_t)fused_pick_splits(s->batch * s->n_kv_heads, tokens, kFusedWaves * 16, (int)n);
         return select_attention_q_dispatch(s, score, q, K, V, qmeta, chunk_off, n_chunks, max_chunks, token_budget, scale,
                                            sel_idx, sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace,
                                            (int)n, stream);
@@ -623,8 +614,7 @@ hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, c
     const size_t cap = (size_t)fused_recommended_splits(s, tokens);
     if (n > cap) n = cap;
     if (n < 1) n = 1;      // a single split needs no partials
-    const int row_bytes = LEOAM_D * (s->kv_dtype == LEOAM_F32 ? 4 : 2);
-    const int n_splits = fused_pick_splits(s->batch * s->n_kv_heads, tokens, 2 * row_bytes, fused_granule(s), (int)n);
+    const int n_splits = fused_pick_splits(s->batch * s->n_kv_heads, tokens, fused_granule(s), (int)n);
     if (s->kv_dtype == LEOAM_F32)
         return fused_by_group<F32>(s, score, q, K, V, chunk_off, n_chunks, max_chunks, token_budget, scale, sel_idx,
                                    sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace, n_splits, exchange,

@@ -1,0 +1,37 @@
+"""Which kernels, and how many splits, the entry points launch for a shape.  The calls are recorded and never run, so
+the results they would compute are the concern of the parity tests."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+TDT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+
+
+@pytest.fixture(scope="module")
+def L():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    import paper_2506_20187_amd as lib
+    return lib
+
+
+def one_call(L, kernels_of, dtype, G, units, budget, n_ctx=16384, c_max=512, k_max=None, max_chunks=0, given=False):
+    """Kernels of chunk_select_attention_decode over `units` (sequence, kv head) pairs."""
+    shape = L.make_shape(units, G, 1, 128, n_ctx, c_max, k_max or c_max, L.binding.Q8Q4 if dtype == "q8q4" else TDT[dtype])
+    t = torch.zeros(64, device="cuda")
+    ws = torch.zeros((L.leoam_fused_workspace_bytes(shape, budget) + 15) // 16 * 16, dtype=torch.uint8, device="cuda")
+    return kernels_of(lambda: L.chunk_select_attention_decode(
+        shape, None if given else t, t, t, t, t, t, max_chunks, budget, 1.0, t, t, t, t, t, ws,
+        qmeta=t if dtype == "q8q4" else None))
+
+
+@pytest.mark.parametrize("given", [False, True], ids=["select", "given"])
+@pytest.mark.parametrize("dtype,G,units,budget,splits", [
+    ("bf16", 4, 128, 1024, 2), ("f16", 1, 128, 512, 2), ("bf16", 2, 96, 512, 2), ("f32", 4, 128, 512, 2),
+    ("bf16", 8, 8, 256, 2), ("bf16", 8, 80, 768, 3), ("bf16", 4, 80, 1536, 3), ("bf16", 4, 40, 3072, 6),
+    ("q8q4", 4, 8, 512, 2), ("q8q4", 1, 128, 2048, 2), ("q8q4", 4, 80, 2048, 3),
+    # one granule or less, more than half of the compute units, more pairs than compute units
+    ("bf16", 4, 8, 256, 1), ("bf16", 4, 8, 1, 1), ("bf16", 4, 129, 4096, 1), ("f32", 1, 192, 4096, 1), ("q8q4", 4, 256, 8192, 1),
+    ("bf16", 4, 512, 4096, 1)])
+def test_splits_fill_one_round_of_workgroups(L, kernels_of, dtype, G, units, budget, splits, given):
+    (name, grid), = one_call(L, kernels_of, dtype, G, units, budget, given=given)
+    assert "select_attention" in name and grid == (splits, 1, units), (name, grid)
