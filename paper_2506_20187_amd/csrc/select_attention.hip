@@ -443,6 +443,7 @@ static inline size_t fused_part_bytes_per_split(const leoam_shape* s) {
     return (size_t)s->batch * s->n_q_heads * kPartStride * sizeof(float);
 }
 
+// Shapes the one-launch kernel can take.
 bool select_attention_is_fused(const leoam_shape* s) {
     // (the kernel adds 32-bit row offsets to a per-(b,h) base: n_ctx rows must stay below 4 GiB)
     return s->kv_dtype != LEOAM_Q8Q4 && s->k_max <= kFusedMaxSel && s->c_max <= 8 * kSelThreads &&
@@ -566,6 +567,29 @@ static int fused_pick_splits(int units, int tokens, int granule, int cap) {
     return (tokens + per_split - 1) / per_split;
 }
 
+// Tokens a call keeps per (b,h), as far as the host can tell: the budget, or without one the most chunks that can be
+// kept, at the average size of c_max chunks.
+static int expected_tokens(const leoam_shape* s, int max_chunks, int token_budget) {
+    if (token_budget > 0) return token_budget < s->n_ctx ? token_budget : s->n_ctx;
+    const long long chunks = max_chunks > 0 && max_chunks < s->k_max ? max_chunks : s->k_max;
+    const long long tokens = chunks * ((s->n_ctx + s->c_max - 1ll) / s->c_max);
+    return tokens < s->n_ctx ? (int)tokens : s->n_ctx;
+}
+
+// Whether a shape that the one-launch kernel can take is also faster there.  With eight heads per group both halves of
+// its waves request every K and V row, so it streams at 3 TB/s where the separate kernels reach 5: it wins as long as
+// what it saves (a launch, two with the merge: 6 to 20 us) is more than that costs.  Microseconds, one launch against
+// separate kernels, bf16: 64 (b,h) x 4096 tokens 48.6 / 50.6, 96 x 3072 53.7 / 53.2, 96 x 4096 66.6 / 60.8, 256 x 1024
+// 48.8 / 50.8, 256 x 1536 67.8 / 61.3; past one workgroup per compute unit 512 x 256 36.1 / 39.8, 384 x 512 49.6 / 44.8,
+// 512 x 4096 360 / 212.  fp32 (the separate kernel multiplies on the vector ALU): 160 x 4096 243 / 257, 192 x 4096
+// 279 / 268, 256 x 2048 176 / 195, 256 x 3072 271 / 268; 512 x 512 96 / 106, 320 x 1024 140 / 137, 512 x 4096 703 / 610.
+static bool one_launch_pays(const leoam_shape* s, int tokens) {
+    if (s->n_q_heads / s->n_kv_heads <= kFusedHeads) return true;
+    const long long units = (long long)s->batch * s->n_kv_heads, total = units * tokens;
+    if (s->kv_dtype == LEOAM_F32) return total <= (units <= kFusedTargetWgs ? 5 << 17 : 1 << 18);
+    return total <= (units <= kFusedTargetWgs ? 1 << 18 : 1 << 17);
+}
+
 hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, const void* q, const void* K,
                                      const void* V, const void* qmeta, const int32_t* chunk_off,
                                      const int32_t* n_chunks, int max_chunks, int token_budget, float scale,
@@ -600,7 +624,7 @@ hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, c
                                            sel_idx, sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace,
                                            (int)n, stream);
     }
-    if (!select_attention_is_fused(s)) {
+    if (!select_attention_is_fused(s) || !one_launch_pays(s, expected_tokens(s, max_chunks, token_budget))) {
         hipError_t e = score ? topk_select_dispatch(s, score, chunk_off, n_chunks, max_chunks, token_budget, sel_idx,
                                                     sel_count, sel_tokens, stream)
                              : hipSuccess;

@@ -765,6 +765,37 @@ def test_one_call_token_count_edges(L, oracle, dtype, G):
             assert np.abs(lse - want_lse).max() <= 1e-4
 
 
+@pytest.mark.parametrize("dtype,B,kept", [("bf16", 4, 8192), ("f16", 33, 496), ("f32", 4, 20480), ("f32", 33, 992)])
+def test_one_call_eight_heads_at_the_change_of_kernels(L, oracle, dtype, B, kept):
+    """Eight heads per group at the largest step that runs in one launch and one token above, where the separate
+    kernels take over (with 32 and with 264 (sequence, kv head) pairs)."""
+    rng = np.random.default_rng(kept)
+    Hkv, G, D, N = 8, 8, 128, kept + 90
+    # (chunks of 16 tokens and one of a single token)
+    off = np.concatenate([np.arange(0, kept + 1, 16), np.arange(kept + 1, N, 16), [N]]).astype(np.int32)
+    packed, counts, c_max = gen.pack_boundaries([off] * B, N)
+    g = torch.Generator(device="cuda").manual_seed(kept)
+    K, V = (torch.randn(B, Hkv, N, D, generator=g, device="cuda").to(TDT[dtype]) for _ in range(2))
+    q = (torch.randn(B, Hkv * G, D, generator=g, device="cuda") * 1.5).to(TDT[dtype])
+    score = (rng.standard_normal((B, Hkv, c_max)) * 20).astype(np.float32)
+    seqs = slice(0, 2)                           # what the oracle checks
+    for budget in (kept, kept + 1):
+        k_max = min(c_max, 2048)
+        sel, cnt, tok, out, lse, _ = gpu_select_attend(L, dtype, score, q, K, V, packed, counts, 0, budget, k_max)
+        want = oracle.topk_select(score, packed, counts, 0, budget, k_max)
+        assert np.array_equal(sel, want[0]) and np.array_equal(cnt, want[1]) and np.array_equal(tok, want[2])
+        want_out, want_lse = oracle.sparse_attention(q[seqs].cpu(), K[seqs].cpu(), V[seqs].cpu(), packed[seqs], sel[seqs], cnt[seqs])
+        assert np.abs(out[seqs] - want_out).max() <= TOL[dtype], budget
+        assert np.abs(lse[seqs] - want_lse).max() <= 1e-4
+        # the other sequences: the separate calls on the GPU (fp32 sums in another order)
+        shape = L.make_shape(B, Hkv * G, Hkv, D, N, c_max, k_max, TDT[dtype])
+        ref, ref_lse = torch.empty(B, Hkv * G, D, device="cuda"), torch.empty(B, Hkv * G, device="cuda")
+        ws = torch.empty(L.leoam_workspace_bytes(shape, budget), dtype=torch.uint8, device="cuda")
+        L.sparse_chunk_attention_decode(shape, q, K, V, dev(packed), dev(counts), dev(sel), dev(cnt), L.default_scale(D), ref,
+                                        ref_lse, ws)
+        assert np.abs(out - ref.cpu().numpy()).max() <= 1e-5 and np.abs(lse - ref_lse.cpu().numpy()).max() <= 1e-4
+
+
 def test_stream_ordered_merge_switch(L, tmp_path):
     """LEOAM_STREAM_ORDERED_MERGE=1 (read once per process, so a child process) makes the one-call entry point run
     the selection, attention and merge kernels back to back: same kept lists bit for bit, outputs within float
