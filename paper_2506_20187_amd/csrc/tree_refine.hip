@@ -36,8 +36,9 @@
 // cores (v_mfma_f64_4x4x4 as in chunk_score.hip: the sixteen B rows are the
 // tokens' key rows, every A block carries the queries), the rows of several
 // such groups in flight; the initial chunks are evaluated eight at a time the
-// same way (many of them: in a launch of their own that fills the chip), with both bounds (B rows 0-7 their kmax rows, rows 8-15 their kmin
-// rows).  To bring the single tokens together the split nodes of a round are
+// same way, with both bounds (B rows 0-7 their kmax rows, rows 8-15 their kmin
+// rows) - many of them, where (sequence, kv head) pairs leave compute units idle,
+// in a launch of their own that fills the chip.  To bring the single tokens together the split nodes of a round are
 // listed in two classes (two-token nodes from the front of the task list, the
 // others from its back).  The evaluation phase dominates: its first rounds are
 // chains of dependent round trips (large nodes, few of them), the later ones are
@@ -54,6 +55,7 @@ constexpr int kTreeCache = 8;          // nodes per thread held in registers thr
 constexpr int kTreeTile = kTreeCache * kTreeThreads;
 constexpr int kTreeWaves = kTreeThreads / LEOAM_WAVE;
 constexpr int kTreeMaxG = 8;
+constexpr int kTreeCus = 256;          // compute units; a refining workgroup fills one
 
 struct alignas(16) TreeNode {
     int32_t start, size;
@@ -875,10 +877,18 @@ hipError_t tree_refine_dispatch(const leoam_shape* s, const void* q, const void*
     // (512 chunks of 16-bit keys, 256 of fp32); up to there its one pass costs no more than a launch.  Measured for the
     // whole call and the attention after it, bf16: 2048 chunks, 8 heads 629 -> 588 us and 128 heads 786 -> 767 us;
     // 1024 chunks, 32 heads 415 -> 400 us.
+    // They get it only if the refining workgroups leave compute units idle (in their last round): otherwise every
+    // workgroup evaluates its own chunks as fast as the launch does, without the launch and without a second trip of the
+    // nodes.  Microseconds of the call, in the workgroups / apart: bf16, 1024 chunks, 128 heads 94.2 / 87.8, 192 95.8 /
+    // 95.8, 224 98.1 / 103.1, 256 100.6 / 106.5; 2048 chunks, 192 heads 164 / 160, 224 170 / 174; 320 heads (a last
+    // round of 64) 191 / 176.  fp32, twice the bytes per chunk: 512 chunks, 128 heads 81.4 / 80.0, 144 81.2 / 84.9;
+    // 1024 chunks, 160 heads 110 / 108, 192 115 / 119.
+    const int last_round = (int)((units - 1) % kTreeCus) + 1;
     const int m0 = (s->n_ctx + chunk_size - 1) / chunk_size;
 #define LEOAM_TREE(TT)                                                                                           \
     const int pass = 8 * kLeafPasses<TT>;                                                                        \
-    const bool apart = G <= 4 && m0 > kTreeWaves * pass;                                                         \
+    const int passes = (m0 + kTreeWaves * pass - 1) / (kTreeWaves * pass);                                       \
+    const bool apart = G <= 4 && passes > 1 && last_round <= (TT::kBytes == 2 ? 192 : passes > 2 ? 160 : 128);   \
     if (apart)                                                                                                   \
         hipLaunchKernelGGL(tree_leaves_kernel<TT>, dim3((m0 + kLeafWaves * pass - 1) / (kLeafWaves * pass),       \
                            s->n_kv_heads, s->batch), dim3(kLeafThreads), 0, stream, (const char*)q,               \

@@ -893,6 +893,17 @@ def test_tree_refine_initial_chunks_in_their_own_launch(L, oracle, dtype, m0, G)
     check_tree(L, oracle, dtype, q, K, 4, 300, 2, N)
 
 
+@pytest.mark.parametrize("dtype,units,m0", [("bf16", 193, 1025), ("f16", 192, 1025), ("f32", 161, 600), ("f32", 129, 400)])
+def test_tree_refine_many_initial_chunks_without_idle_compute_units(L, oracle, dtype, units, m0):
+    """Several passes of a refining workgroup over its initial chunks, around the number of pairs from which these are no
+    longer evaluated apart."""
+    g = torch.Generator().manual_seed(units)
+    N = 2 * m0 - 1
+    K = torch.randn(1, units, N, 128, generator=g).to(TDT[dtype])
+    q = torch.randn(1, units * 2, 128, generator=g).to(TDT[dtype])
+    check_tree(L, oracle, dtype, q, K, 2, 100, 1, N)
+
+
 @pytest.mark.parametrize("seed", list(range(16)))
 def test_tree_refine_random_shapes(L, oracle, seed):
     """Shapes and data drawn at random (seeded): dtype, group size, ragged context, initial chunk size, k, round limit,

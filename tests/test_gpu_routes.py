@@ -46,3 +46,18 @@ def test_eight_heads_per_group_leave_the_one_launch_kernel_for_large_steps(L, ke
         assert (len(names) == 1 and "select_attention" in names[0]) == fused, (budget, max_chunks, names)
         assert ("topk_select" in names[0]) != fused, names
     assert len(one_call(L, kernels_of, dtype, 4, units, 65536, n_ctx=65536, c_max=1024)) == 1
+
+
+@pytest.mark.parametrize("dtype,G,units,m0,apart", [
+    ("bf16", 4, 8, 513, True), ("bf16", 4, 8, 512, False), ("f32", 1, 8, 257, True), ("f32", 1, 8, 256, False),
+    ("bf16", 8, 8, 2048, False),
+    ("bf16", 4, 192, 2048, True), ("f16", 1, 193, 2048, False), ("bf16", 2, 256, 2048, False), ("bf16", 4, 320, 1024, True),
+    ("bf16", 4, 512, 2048, False), ("f32", 1, 128, 512, True), ("f32", 1, 129, 512, False), ("f32", 4, 160, 513, True),
+    ("f32", 4, 161, 2048, False)])
+def test_tree_initial_chunks_apart_where_compute_units_are_idle(L, kernels_of, dtype, G, units, m0, apart):
+    shape = L.make_shape(1, units * G, units, 128, 4 * m0, m0, m0, TDT[dtype])
+    t = torch.zeros(64, device="cuda")
+    ws = torch.empty(L.leoam_tree_workspace_bytes(shape, m0), dtype=torch.uint8, device="cuda")
+    launched = kernels_of(lambda: L.chunk_tree_refine(shape, t, t, t, 4, 16, 1, m0, t, t, t, t, t, ws))
+    assert ["tree_leaves" in n for n, _ in launched] == ([True, False] if apart else [False])
+    assert "tree_refine" in launched[-1][0] and launched[-1][1] == (units, 1, 1)
