@@ -548,11 +548,18 @@ def test_path_random_shapes(L, oracle, seed):
     check_path(L, oracle, case, separate=bool(rng.integers(2)))
 
 
-def test_path_two_splits_per_head(L, oracle):
+def test_path_two_splits_per_head(L, oracle, kernels_of):
     """16 sequences x 8 kv heads: two workgroups per (sequence, kv head), combined through the exchange words of the
     workspace (one atomic exchange per output element); ragged context, small budget."""
     case = gen.make_case("c3", layer=20, batch=16, n_ctx=4096 + 37, hq=32, hkv=8, token_budget=768)
     check_path(L, oracle, case)
+    layer, q = run_path(L, case), case.q.cuda()
+    grids = [g for n, g in kernels_of(lambda: layer.step(q)) if "select_attention_kernel" in n]
+    assert grids == [(2, 8, 16)], grids
+    layer.sel_count.zero_()                               # two workgroups, empty lists
+    layer.attend_given(q)
+    assert torch.all(layer.out == 0) and torch.all(torch.isneginf(layer.lse))
+    assert not layer.workspace[: L.leoam_fused_control_bytes(layer.shape)].any()
     case = gen.make_case("c3", layer=2, batch=16, n_ctx=2048 + 5, hq=16, hkv=8, token_budget=8)      # nothing fits
     layer = run_path(L, case)
     assert int(layer.sel_count.abs().sum()) == 0 and torch.all(layer.out == 0) and torch.all(torch.isneginf(layer.lse))
@@ -763,6 +770,56 @@ def test_one_call_token_count_edges(L, oracle, dtype, G):
             assert np.array_equal(sel, want_sel) and np.array_equal(cnt, want_cnt) and np.array_equal(tok, want_tok)
             assert np.abs(out - want_out).max() <= TOL[dtype], f"kept={kept} max_chunks={max_chunks}"
             assert np.abs(lse - want_lse).max() <= 1e-4
+
+
+@pytest.mark.parametrize("over", ["k_max", "c_max"])
+@pytest.mark.parametrize("dtype,G", [("bf16", 4), ("f16", 1), ("bf16", 8), ("f32", 1), ("f32", 4), ("f32", 8)])
+def test_one_call_over_the_tables_of_the_one_launch_kernel(L, oracle, kernels_of, dtype, G, over):
+    """Rows for more kept chunks (k_max > 2048) or more chunks (c_max > 8192) than the one-launch kernel has room for: the
+    selection and the split attention kernel, which merges up to 16 splits itself with the workspace's counters and
+    leaves more to the merge kernel.  With a score row and with the kept lists given."""
+    rng = np.random.default_rng(70 + G)
+    B, Hkv, D, C = 2, 2, 128, 2600
+    off = np.concatenate([[0], np.cumsum(rng.integers(1, 9, size=C))]).astype(np.int32)
+    N = int(off[-1])
+    packed, counts, c_max = gen.pack_boundaries([off, off], N, 8193 if over == "c_max" else None)
+    k_max = 2049 if over == "k_max" else 1000
+    g = torch.Generator().manual_seed(G)
+    K, V = (torch.randn(B, Hkv, N, D, generator=g).to(TDT[dtype]) for _ in range(2))
+    q = (torch.randn(B, Hkv * G, D, generator=g) * 1.5).to(TDT[dtype])
+    score = (rng.standard_normal((B, Hkv, c_max)) * 20).astype(np.float32)
+    shape = L.make_shape(B, Hkv * G, Hkv, D, N, c_max, k_max, TDT[dtype])
+    head, part = L.leoam_fused_control_bytes(shape), B * Hkv * G * (D + 2) * 4
+    dq, dK, dV, doff, dnc, dscore = (dev(t) for t in (q, K, V, packed, counts, score))
+    for max_chunks, budget in ((0, N // 2), (0, 3), (90, 0)):
+        # the library caps the count at k_max; the oracle takes that cap as max_chunks
+        want_sel, want_cnt, want_tok = oracle.topk_select(score, packed, counts, max_chunks or k_max, budget, k_max)
+        want_out, want_lse = oracle.sparse_attention(q, K, V, packed, want_sel, want_cnt)
+        for n_splits in (1, 2, 9, 16, 17):
+            ws = torch.zeros(head + n_splits * part, dtype=torch.uint8, device="cuda")
+            sel, cnt = torch.full((B, Hkv, k_max), -7, dtype=torch.int32, device="cuda"), torch.zeros(B, Hkv, dtype=torch.int32, device="cuda")
+            tok, first = torch.full_like(cnt, -7), None
+            for given in (False, False, True):
+                ws[head:] = 0xFF
+                out, lse = torch.full((B, Hkv * G, D), float("nan"), device="cuda"), torch.full((B, Hkv * G), float("nan"), device="cuda")
+
+                def call():
+                    L.chunk_select_attention_decode(shape, None if given else dscore, dq, dK, dV, doff, dnc, max_chunks, budget,
+                                                    L.default_scale(D), sel, cnt, tok, out, lse, ws)
+                names = [n for n, _ in kernels_of(call)]
+                assert [k for k in ("topk_select", "sparse_attention", "attention_merge") if any(k in n for n in names)] == \
+                    ["topk_select"] * (not given) + ["sparse_attention"] + ["attention_merge"] * (n_splits > 16), names
+                call()
+                tag = f"max_chunks={max_chunks} budget={budget} splits={n_splits} given={given}"
+                assert np.array_equal(sel.cpu().numpy(), want_sel) and np.array_equal(cnt.cpu().numpy(), want_cnt), tag
+                assert np.array_equal(tok.cpu().numpy(), want_tok), tag
+                assert np.abs(host_f64(out) - want_out).max() <= TOL[dtype], tag
+                fin = np.isfinite(want_lse)
+                assert np.array_equal(np.isneginf(host_f64(lse)), ~fin), tag
+                assert not fin.any() or np.abs(host_f64(lse)[fin] - want_lse[fin]).max() <= 1e-4, tag
+                assert not ws[:head].any(), tag                      # counters are back at zero
+                first = (out, lse) if first is None else first
+                assert torch.equal(out, first[0]) and torch.equal(lse, first[1]), tag
 
 
 @pytest.mark.parametrize("dtype,B,kept", [("bf16", 4, 8192), ("f16", 33, 496), ("f32", 4, 20480), ("f32", 33, 992)])

@@ -3,6 +3,8 @@ counters and split partials live in a buffer inside the library image) against c
 on the same inputs: kept lists bit-exact, outputs bit-exact when both run the same number of splits
 (the merge order is fixed), and both against the oracle.  Calls in a row with different shapes share the
 buffer: a large batch first, then smaller inputs whose counters lie where the first call's partials were."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -52,19 +54,25 @@ def both_ways(L, oracle, case):
 
 def test_static_workspace_calls_in_a_row(L, oracle):
     # 48 (sequence, kv head) pairs, two splits each; then one sequence with two kv heads (many splits; its
-    # counters and first partials lie where the first call left partials); then the fp32 shape that takes the
-    # two-launch path; then the first shape again
+    # counters and first partials lie where the first call left partials); then fp32; then a table for more kept
+    # chunks than the one-launch kernel has room for, which takes the separate kernels; then the first shapes again
     big = gen.make_case("c3", layer=9, batch=6, n_ctx=8192 + 100, hq=32, hkv=8, token_budget=1024)
     small = gen.make_case("c2", layer=17, n_ctx=4096 + 5, hq=8, hkv=2, token_budget=512)
     tiny = gen.make_case("c0")
-    for case in (big, small, tiny, big, small):
+    wide = dataclasses.replace(gen.make_case("c2", layer=13, n_ctx=65536, hq=8, hkv=2, token_budget=2048), k_max=2049)
+    for case in (big, small, tiny, wide, big, small):
         assert both_ways(L, oracle, case)
 
 
-def test_static_workspace_refuses_what_does_not_fit(L):
+@pytest.mark.parametrize("dtype,G,c_max,k_max", [
+    # the separate kernels (more kept chunks, more chunks than the one-launch kernel has room for)
+    (torch.bfloat16, 4, 4096, 2049), (torch.float16, 1, 8193, 64), (torch.float32, 2, 4096, 2049),
+    # fp32 and eight heads per group ask for that workspace whichever kernels would run
+    (torch.float32, 1, 64, 64), (torch.bfloat16, 8, 64, 64)])
+def test_static_workspace_refuses_what_does_not_fit(L, dtype, G, c_max, k_max):
     t = torch.zeros(64, device="cuda")
-    # fp32 takes the two-launch path: its smallest workspace is one partial per (b, q head) = 520 bytes each
-    shape = L.make_shape(2048, 8, 8, 128, 4096, 64, 64, torch.float32)
+    # the smallest workspace is one partial per (b, q head) = 520 bytes each
+    shape = L.make_shape(2048, 8, 8 // G, 128, 4096, c_max, k_max, dtype)
     assert 2048 * 8 * 520 > L.binding.STATIC_SCRATCH_BYTES
     with pytest.raises(L.LeoamError) as e:
         L.chunk_select_attention_decode_static(shape, t, t, t, t, t, t, 0, 0, 1.0, t, t, t, t, None)
