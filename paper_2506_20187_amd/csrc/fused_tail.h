@@ -115,9 +115,12 @@ __device__ __forceinline__ void fused_tail(float (*xw)[kHeads][kPartStride], int
                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             float os[kW];
 #pragma unroll
-            for (int i = 0; i < kW; ++i)      // (past the end: the last split's, with weight 0)
+            for (int i = 0; i < kW; ++i)
                 os[i] = __hip_atomic_load(&base[(size_t)min(s0 + i, n_splits - 1) * kPartStride + d], __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int i = 0; i < kW; ++i)      // (past the end the weight is 0, the last split's value may be infinite)
+                if (s0 + i >= n_splits) os[i] = 0.f;
             state.fold<kW>(real ? bits_to_float((uint32_t)ml) : -INFINITY, real ? bits_to_float((uint32_t)(ml >> 32)) : 0.f,
                            [&](int i) { return os[i]; });
         };

@@ -74,6 +74,14 @@ template <> __device__ __forceinline__ uint4 pack<F16>(const float* x) {
 __device__ __forceinline__ uint4 load16(const void* base, size_t byte_off) {
     return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base) + byte_off);
 }
+// `bytes` bytes at a uniform address as a raw buffer: a load past its end gets zeros and makes no access.
+using buffer_t = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ buffer_t buffer_of(const char* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), 0, (int)bytes, 0x00027000);
+}
+__device__ __forceinline__ uint4 buffer_load16(buffer_t b, uint32_t byte_off) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)byte_off, 0, 0));
+}
 __device__ __forceinline__ void store16(void* base, size_t byte_off, const uint4& v) {
     *reinterpret_cast<uint4*>(reinterpret_cast<char*>(base) + byte_off) = v;
 }

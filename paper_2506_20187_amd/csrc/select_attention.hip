@@ -207,9 +207,9 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
     const int per_wave = per_split / P::kStreams, part = P::kParts == 1 ? 0 : wave / P::kStreams;
     const int w0 = min(r1, r0 + (wave % P::kStreams) * per_wave), w1 = min(r1, w0 + per_wave);
 
-    // uniform bases; a lane adds a 32-bit offset (n_ctx rows stay below 4 GiB)
-    const char* Kbh = K + bh * (size_t)n_ctx * ROWB;
-    const char* Vbh = V + bh * (size_t)n_ctx * ROWB;
+    // the (b,h)'s rows as buffers; a lane adds a 32-bit offset (n_ctx + 1 rows stay below 4 GiB)
+    const buffer_t Kbh = buffer_of(K + bh * (size_t)n_ctx * ROWB, (uint32_t)n_ctx * ROWB);
+    const buffer_t Vbh = buffer_of(V + bh * (size_t)n_ctx * ROWB, (uint32_t)n_ctx * ROWB);
     const uint32_t k_lane = 16u * grp, v_lane = 16u * c16;
     int32_t* my_rows = ph.rows[wave];
 
@@ -222,17 +222,18 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
 #pragma unroll
         for (int e = 0; e < NACC; ++e) acc[g][e] = 0.f;
 
-    // Loads are unconditional (a load under a condition is waited for on its own):
-    // a position past the end reads the block's last row (`end`), its logit is masked to -inf, its weight is 0.
-    auto fetch = [&](int t, FusedKvTile<T>& kv, int end) {
-        const int krow = my_rows[min(16 * t + c16, end)];
+    // Loads are unconditional (a load under a condition is waited for on its own): a position past the end has row
+    // n_ctx, which is outside the buffers, and gets zeros without an access.  (Its logit is masked to -inf; a weight of
+    // 0 would not be enough, as 0 times a kept row's infinity is not 0.)
+    auto fetch = [&](int t, FusedKvTile<T>& kv) {
+        const uint32_t krow = my_rows[16 * t + c16];
 #pragma unroll
-        for (int s = 0; s < KP; ++s) kv.k[s] = load16(Kbh, (size_t)((uint32_t)krow * ROWB + k_lane + 64u * s));
+        for (int s = 0; s < KP; ++s) kv.k[s] = buffer_load16(Kbh, krow * ROWB + k_lane + 64u * s);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int vrow = my_rows[min(16 * t + 4 * grp + i, end)];
+            const uint32_t vrow = my_rows[16 * t + 4 * grp + i];
 #pragma unroll
-            for (int s = 0; s < VP; ++s) kv.v[i][s] = load16(Vbh, (size_t)((uint32_t)vrow * ROWB + v_lane + 256u * s));
+            for (int s = 0; s < VP; ++s) kv.v[i][s] = buffer_load16(Vbh, vrow * ROWB + v_lane + 256u * s);
         }
     };
     int q_lane = lane;
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
             }
 #pragma unroll
             for (int j = 0; j < PER; ++j) {
-                int p = 0;
+                int p = n_ctx;
                 if (i0 + j < nb) {
                     const int x = blk + i0 + j;
                     while (prefix[lo + 1] <= x) ++lo;      // ends: prefix[cnt] = total > x
@@ -342,13 +343,13 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
             // do not fit the registers
             for (int t = 0; t < n_tiles; ++t) {
                 FusedKvTile<T> cur;
-                fetch(t, cur, nb - 1);
+                fetch(t, cur);
                 accumulate(logits(cur.k), cur.v, nb - 16 * t);
             }
             continue;
         }
         FusedKvTile<T> cur, nxt;
-        fetch(0, cur, nb - 1);
+        fetch(0, cur);
         if (n_tiles == 1) {
             // a single tile (small batches spread a (b,h) over many workgroups): nothing to prefetch,
             // and the pipeline's re-reads of the last tile would triple the load instructions
@@ -357,10 +358,10 @@ __global__ __launch_bounds__(kSelThreads) void select_attention_kernel(
         }
         for (int t = 0; t < n_tiles; t += 2) {
             // (no loads under a condition: a tile index past the end re-reads the last tile)
-            fetch(min(t + 1, last), nxt, nb - 1);
+            fetch(min(t + 1, last), nxt);
             __builtin_amdgcn_sched_barrier(0);       // keep the loads ahead of the tile's arithmetic
             accumulate(logits(cur.k), cur.v, nb - 16 * t);
-            fetch(min(t + 2, last), cur, nb - 1);
+            fetch(min(t + 2, last), cur);
             __builtin_amdgcn_sched_barrier(0);
             if (t + 1 < n_tiles) accumulate(logits(nxt.k), nxt.v, nb - 16 * (t + 1));
         }

@@ -772,6 +772,38 @@ def test_one_call_token_count_edges(L, oracle, dtype, G):
             assert np.abs(lse - want_lse).max() <= 1e-4
 
 
+@pytest.mark.parametrize("dtype,G", [("f32", 1), ("f32", 4), ("f32", 8), ("bf16", 4), ("bf16", 8), ("f16", 1)])
+def test_one_call_keeps_infinite_values_apart(L, oracle, dtype, G):
+    """Values at infinity in kept rows (every one of them in channel 0, only the last one in channel 1) show in their own
+    channel as infinities and nowhere else, whatever a tile or a batch of partials is padded with; rows that are not kept
+    hold NaN."""
+    rng = np.random.default_rng(51 + G)
+    B, Hkv, D, N = 1, 2, 128, 1400
+    packed, counts, c_max = gen.pack_boundaries([np.arange(N + 1, dtype=np.int32)], N)      # chunks of one token
+    K = rng.standard_normal((B, Hkv, N, D)).astype(np.float32)
+    V = rng.standard_normal((B, Hkv, N, D)).astype(np.float32)
+    q = torch.from_numpy(rng.standard_normal((B, Hkv * G, D)).astype(np.float32)).to(TDT[dtype])
+    score = rng.permutation(B * Hkv * c_max).reshape(B, Hkv, c_max).astype(np.float32)
+    for kept in (1, 17, 130, 257, 600, 1300):
+        sel, cnt, _ = oracle.topk_select(score, packed, counts, 0, kept, 1400)
+        k, v, ref = K.copy(), V.copy(), V.copy()
+        ref[..., :2] = 0
+        for h in range(Hkv):
+            rows = sel[0, h, : cnt[0, h]]
+            away = np.setdiff1d(np.arange(N), rows)
+            k[0, h, away] = v[0, h, away] = np.nan
+            v[0, h, rows, 0] = np.inf
+            v[0, h, rows[-1], 1] = -np.inf
+        k, v, ref = (torch.from_numpy(t).to(TDT[dtype]) for t in (k, v, ref))
+        want, want_lse = oracle.sparse_attention(q, torch.nan_to_num(k, nan=0.0), ref, packed, sel, cnt)
+        for n_splits in (None, 1, 3, 5):
+            _, _, _, out, lse, _ = gpu_select_attend(L, dtype, score, q, k, v, packed, counts, 0, kept, 1400, n_splits=n_splits)
+            tag = f"kept={kept} n_splits={n_splits}"
+            assert np.all(np.isposinf(out[..., 0])) and np.all(np.isneginf(out[..., 1])), tag
+            assert np.abs(out[..., 2:] - want[..., 2:]).max() <= TOL[dtype], tag
+            assert np.abs(lse - want_lse).max() <= 1e-4, tag
+
+
 @pytest.mark.parametrize("over", ["k_max", "c_max"])
 @pytest.mark.parametrize("dtype,G", [("bf16", 4), ("f16", 1), ("bf16", 8), ("f32", 1), ("f32", 4), ("f32", 8)])
 def test_one_call_over_the_tables_of_the_one_launch_kernel(L, oracle, kernels_of, dtype, G, over):
