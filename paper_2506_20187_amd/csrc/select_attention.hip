@@ -29,6 +29,7 @@
 // groups is taken with lane swaps on the vector ALU (two ds_bpermute round trips
 // per tile in its place cost the launch 10 % on MI355X, the next tile's loads
 // queue behind the same waits).
+#include <algorithm>
 #include <cstdlib>
 
 #include "fused_tail.h"
@@ -577,18 +578,30 @@ static int expected_tokens(const leoam_shape* s, int max_chunks, int token_budge
     return tokens < s->n_ctx ? (int)tokens : s->n_ctx;
 }
 
-// Whether a shape that the one-launch kernel can take is also faster there.  With eight heads per group both halves of
+// Whether a shape that the one-launch kernel can take is also faster there (`even`: the lists of all (b,h) hold about
+// the same number of tokens, as with a budget).  With eight heads per group both halves of
 // its waves request every K and V row, so it streams at 3 TB/s where the separate kernels reach 5: it wins as long as
 // what it saves (a launch, two with the merge: 6 to 20 us) is more than that costs.  Microseconds, one launch against
 // separate kernels, bf16: 64 (b,h) x 4096 tokens 48.6 / 50.6, 96 x 3072 53.7 / 53.2, 96 x 4096 66.6 / 60.8, 256 x 1024
 // 48.8 / 50.8, 256 x 1536 67.8 / 61.3; past one workgroup per compute unit 512 x 256 36.1 / 39.8, 384 x 512 49.6 / 44.8,
 // 512 x 4096 360 / 212.  fp32 (the separate kernel multiplies on the vector ALU): 160 x 4096 243 / 257, 192 x 4096
 // 279 / 268, 256 x 2048 176 / 195, 256 x 3072 271 / 268; 512 x 512 96 / 106, 320 x 1024 140 / 137, 512 x 4096 703 / 610.
-static bool one_launch_pays(const leoam_shape* s, int tokens) {
+// Where the splits do not divide the compute units well it also loses by the length of a workgroup's share: 129 (b,h),
+// one split each, bf16 1200 tokens 43.5 / 44.8, 1400 48.2 / 47.3, 2000 61.2 / 54.2; 86 (b,h), two splits, 2048 tokens
+// 39.9 / 42.9, 2600 51.0 / 47.2; 257 (b,h) 320 tokens 34.7 / 34.4, 448 41.5 / 38.4; fp32 129 (b,h) 2000 tokens
+// 117 / 129, 3000 177 / 168, 5000 309 / 260; 257 (b,h) 640 tokens 86.6 / 90.2, 1000 131 / 122.
+// Without a budget the lists differ in length and the longest, about 4/3 of the average, sets the pace of a round
+// of whole lists: bf16, 160 (b,h), chunk limit of 12 (876 tokens on average) 41.8 / 42.7, of 16 51.0 / 47.2; 130 (b,h),
+// limit of 24 64.5 / 52.9.
+static bool one_launch_pays(const leoam_shape* s, int tokens, bool even) {
     if (s->n_q_heads / s->n_kv_heads <= kFusedHeads) return true;
     const long long units = (long long)s->batch * s->n_kv_heads, total = units * tokens;
-    if (s->kv_dtype == LEOAM_F32) return total <= (units <= kFusedTargetWgs ? 5 << 17 : 1 << 18);
-    return total <= (units <= kFusedTargetWgs ? 1 << 18 : 1 << 17);
+    const bool one_round = units <= kFusedTargetWgs;
+    const int splits = one_round ? kFusedTargetWgs / (int)units : 1;
+    int share = (tokens + splits - 1) / splits;
+    if (s->kv_dtype == LEOAM_F32) return share <= (one_round ? 3072 : 800) && total <= (one_round ? 5 << 17 : 1 << 18);
+    if (!even && splits == 1) share = (int)std::min((share * 4ll + 2) / 3, (long long)s->n_ctx);
+    return share <= (one_round ? 1200 : 320) && total <= (one_round ? 1 << 18 : 1 << 17);
 }
 
 hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, const void* q, const void* K,
@@ -625,7 +638,7 @@ hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, c
                                            sel_idx, sel_count, sel_tokens, out, lse, (float*)body, (int32_t*)workspace,
                                            (int)n, stream);
     }
-    if (!select_attention_is_fused(s) || !one_launch_pays(s, expected_tokens(s, max_chunks, token_budget))) {
+    if (!select_attention_is_fused(s) || !one_launch_pays(s, expected_tokens(s, max_chunks, token_budget), token_budget > 0)) {
         hipError_t e = score ? topk_select_dispatch(s, score, chunk_off, n_chunks, max_chunks, token_budget, sel_idx,
                                                     sel_count, sel_tokens, stream)
                              : hipSuccess;

@@ -37,15 +37,19 @@ def test_splits_fill_one_round_of_workgroups(L, kernels_of, dtype, G, units, bud
     assert "select_attention" in name and grid == (splits, 1, units), (name, grid)
 
 
-@pytest.mark.parametrize("dtype,units,tokens", [("bf16", 8, 32768), ("f16", 32, 8192), ("bf16", 256, 1024), ("bf16", 257, 510),
-                                                ("f32", 32, 20480), ("f32", 256, 2560), ("f32", 264, 992)])
-def test_eight_heads_per_group_leave_the_one_launch_kernel_for_large_steps(L, kernels_of, dtype, units, tokens):
-    chunks = tokens // 64                     # without a budget: chunks of n_ctx / c_max = 64 tokens
+@pytest.mark.parametrize("dtype,units,tokens,chunks", [
+    # the most tokens of a step
+    ("bf16", 8, 32768, 512), ("f16", 32, 8192, 128), ("bf16", 256, 1024, 14), ("f32", 32, 20480, 320), ("f32", 256, 2560, 40),
+    ("bf16", 512, 256, 3), ("f32", 512, 512, 8),
+    # the most tokens of a workgroup's share
+    ("bf16", 86, 2400, 37), ("bf16", 129, 1200, 14), ("f16", 200, 1200, 14), ("f32", 129, 3072, 48), ("f32", 86, 6144, 96),
+    ("bf16", 257, 320, 3), ("f16", 384, 320, 3), ("f32", 257, 800, 12), ("f32", 327, 800, 12)])
+def test_eight_heads_per_group_leave_the_one_launch_kernel_for_large_steps(L, kernels_of, dtype, units, tokens, chunks):
+    """The largest budget and, without a budget, the largest chunk limit (chunks of n_ctx / c_max = 64 tokens)."""
     for budget, max_chunks, fused in ((tokens, 0, True), (tokens + 1, 0, False), (0, chunks, True), (0, chunks + 1, False)):
         names = [n for n, _ in one_call(L, kernels_of, dtype, 8, units, budget, n_ctx=65536, c_max=1024, max_chunks=max_chunks)]
         assert (len(names) == 1 and "select_attention" in names[0]) == fused, (budget, max_chunks, names)
         assert ("topk_select" in names[0]) != fused, names
-    assert len(one_call(L, kernels_of, dtype, 4, units, 65536, n_ctx=65536, c_max=1024)) == 1
 
 
 @pytest.mark.parametrize("dtype,G,units,m0,apart", [
