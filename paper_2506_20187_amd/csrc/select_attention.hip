@@ -578,6 +578,27 @@ static int expected_tokens(const leoam_shape* s, int max_chunks, int token_budge
     return tokens < s->n_ctx ? (int)tokens : s->n_ctx;
 }
 
+// fp32, up to four heads per group: a workgroup has its compute unit to itself, while three of the separate kernel's
+// share one, so the one launch loses where few workgroups run last.  Microseconds, one launch against separate kernels,
+// 4096 tokens, one head: 256 (b,h) 184 / 198, 257 271 / 217, 320 281 / 249, 384 297 / 288, 400 298 / 328, 512 356 / 379,
+// 528 449 / 420, 608 461 / 452, 640 467 / 467; two heads: 257 272 / 223, 336 287 / 263, 400 301 / 338, 528 450 / 441;
+// four heads: 257 281 / 265, 304 290 / 302.  Short lists gain more from the launch that is saved (257 (b,h): two heads
+// 256 tokens 25.6 / 26.9, 384 34.2 / 32.6, four heads 512 tokens 46.5 / 48.4, 768 64.8 / 61.1), unless a compute unit
+// takes many one after the other: one head, 1024 (b,h) 128 tokens 43.2 / 37.2, 256 62.4 / 58.9, 512 107 / 106, 768
+// 149 / 153; 700 (b,h) 64 tokens 21.8 / 18.8, 128 32.6 / 33.3; two heads 1024 (b,h) 128 tokens 44.1 / 39.7, 256 63.4 /
+// 62.2, 384 86.9 / 86.9; four heads 1100 (b,h) 64 tokens 36.3 / 33.6, 192 66.0 / 66.7.
+// Little more than half as many lists as compute units, of uneven length: one head, 24 chunks (1752 tokens on average)
+// 129 (b,h) 71.1 / 61.8, 144 67.7 / 65.7, 156 69.0 / 69.7; 12 chunks 132 39.9 / 39.5; two heads 129 67.6 / 64.4, 140
+// 67.6 / 69.7.
+static bool one_launch_pays_f32(int G, long long units, int tokens, bool even) {
+    const long long rounds = (units + kFusedTargetWgs - 1) / kFusedTargetWgs, last = (units - 1) % kFusedTargetWgs + 1;
+    const long long over_half = units - kFusedTargetWgs / 2;
+    if (rounds == 1) return even || G > 2 || over_half <= 0 || over_half * G > 24 || tokens < 1024 * G;
+    if (rounds == 2) return last > (G == 1 ? 128 : G == 2 ? 80 : 32) || tokens < 192 * G;
+    if (rounds == 3) return G > 2 || (tokens > 96 && (G == 2 || last > 128));
+    return tokens > (G == 1 ? 512 : G == 2 ? 256 : 96);
+}
+
 // Whether a shape that the one-launch kernel can take is also faster there (`even`: the lists of all (b,h) hold about
 // the same number of tokens, as with a budget).  With eight heads per group both halves of
 // its waves request every K and V row, so it streams at 3 TB/s where the separate kernels reach 5: it wins as long as
@@ -592,16 +613,18 @@ static int expected_tokens(const leoam_shape* s, int max_chunks, int token_budge
 // 117 / 129, 3000 177 / 168, 5000 309 / 260; 257 (b,h) 640 tokens 86.6 / 90.2, 1000 131 / 122.
 // Without a budget the lists differ in length and the longest, about 4/3 of the average, sets the pace of a round
 // of whole lists: bf16, 160 (b,h), chunk limit of 12 (876 tokens on average) 41.8 / 42.7, of 16 51.0 / 47.2; 130 (b,h),
-// limit of 24 64.5 / 52.9.
+// limit of 24 64.5 / 52.9.  Many short lists: 800 (b,h), 96 tokens 34.0 / 36.2, 128 40.9 / 39.3, limit of 2 52.5 / 44.9.
 static bool one_launch_pays(const leoam_shape* s, int tokens, bool even) {
-    if (s->n_q_heads / s->n_kv_heads <= kFusedHeads) return true;
-    const long long units = (long long)s->batch * s->n_kv_heads, total = units * tokens;
-    const bool one_round = units <= kFusedTargetWgs;
-    const int splits = one_round ? kFusedTargetWgs / (int)units : 1;
-    int share = (tokens + splits - 1) / splits;
-    if (s->kv_dtype == LEOAM_F32) return share <= (one_round ? 3072 : 800) && total <= (one_round ? 5 << 17 : 1 << 18);
-    if (!even && splits == 1) share = (int)std::min((share * 4ll + 2) / 3, (long long)s->n_ctx);
-    return share <= (one_round ? 1200 : 320) && total <= (one_round ? 1 << 18 : 1 << 17);
+    const int G = s->n_q_heads / s->n_kv_heads;
+    const long long units = (long long)s->batch * s->n_kv_heads;
+    if (G <= kFusedHeads) return s->kv_dtype != LEOAM_F32 || one_launch_pays_f32(G, units, tokens, even);
+    const long long rounds = (units + kFusedTargetWgs - 1) / kFusedTargetWgs;
+    const int splits = rounds == 1 ? kFusedTargetWgs / (int)units : 1;
+    if (s->kv_dtype == LEOAM_F32)
+        return (tokens + splits - 1) / splits <= (rounds == 1 ? 3072 : 800) && units * tokens <= (rounds == 1 ? 5 << 17 : 1 << 18);
+    if (!even && splits == 1) tokens = (int)std::min((tokens * 4ll + 2) / 3, (long long)s->n_ctx);
+    return (tokens + splits - 1) / splits <= (rounds == 1 ? 1200 : rounds <= 3 ? 320 : 96) &&
+           units * tokens <= (rounds == 1 ? 1 << 18 : 1 << 17);
 }
 
 hipError_t select_attention_dispatch(const leoam_shape* s, const float* score, const void* q, const void* K,

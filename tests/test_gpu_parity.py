@@ -854,13 +854,14 @@ def test_one_call_over_the_tables_of_the_one_launch_kernel(L, oracle, kernels_of
                 assert torch.equal(out, first[0]) and torch.equal(lse, first[1]), tag
 
 
-@pytest.mark.parametrize("dtype,B,kept", [("bf16", 4, 8192), ("f16", 33, 320), ("f32", 4, 20480), ("f32", 33, 800)])
-def test_one_call_eight_heads_at_the_change_of_kernels(L, oracle, dtype, B, kept):
-    """Eight heads per group at the largest step that runs in one launch and one token above, where the separate
-    kernels take over (with 32 and with 264 (sequence, kv head) pairs)."""
+@pytest.mark.parametrize("dtype,B,G,kept", [("bf16", 4, 8, 8192), ("f16", 33, 8, 320), ("f32", 4, 8, 20480), ("f32", 33, 8, 800),
+                                            ("f32", 33, 1, 191), ("f32", 33, 2, 383), ("f32", 33, 4, 767)])
+def test_one_call_at_the_change_of_kernels(L, oracle, dtype, B, G, kept):
+    """The largest step that runs in one launch and one token above, where the separate kernels take over (with 32 and
+    with 264 (sequence, kv head) pairs)."""
     rng = np.random.default_rng(kept)
-    Hkv, G, D, N = 8, 8, 128, kept + 90
-    # (chunks of 16 tokens and one of a single token)
+    Hkv, D, N = 8, 128, kept + 90
+    # (chunks of 16 tokens and shorter ones)
     off = np.concatenate([np.arange(0, kept + 1, 16), np.arange(kept + 1, N, 16), [N]]).astype(np.int32)
     packed, counts, c_max = gen.pack_boundaries([off] * B, N)
     g = torch.Generator(device="cuda").manual_seed(kept)

@@ -39,17 +39,38 @@ def test_splits_fill_one_round_of_workgroups(L, kernels_of, dtype, G, units, bud
 
 @pytest.mark.parametrize("dtype,units,tokens,chunks", [
     # the most tokens of a step
-    ("bf16", 8, 32768, 512), ("f16", 32, 8192, 128), ("bf16", 256, 1024, 14), ("f32", 32, 20480, 320), ("f32", 256, 2560, 40),
+    ("bf16", 8, 32768, 512), ("f16", 32, 8192, 128), ("bf16", 256, 1024, 12), ("f32", 32, 20480, 320), ("f32", 256, 2560, 40),
     ("bf16", 512, 256, 3), ("f32", 512, 512, 8),
     # the most tokens of a workgroup's share
     ("bf16", 86, 2400, 37), ("bf16", 129, 1200, 14), ("f16", 200, 1200, 14), ("f32", 129, 3072, 48), ("f32", 86, 6144, 96),
-    ("bf16", 257, 320, 3), ("f16", 384, 320, 3), ("f32", 257, 800, 12), ("f32", 327, 800, 12)])
+    ("bf16", 257, 320, 3), ("f16", 384, 320, 3), ("f32", 257, 800, 12), ("f32", 327, 800, 12), ("bf16", 769, 96, 1)])
 def test_eight_heads_per_group_leave_the_one_launch_kernel_for_large_steps(L, kernels_of, dtype, units, tokens, chunks):
     """The largest budget and, without a budget, the largest chunk limit (chunks of n_ctx / c_max = 64 tokens)."""
     for budget, max_chunks, fused in ((tokens, 0, True), (tokens + 1, 0, False), (0, chunks, True), (0, chunks + 1, False)):
         names = [n for n, _ in one_call(L, kernels_of, dtype, 8, units, budget, n_ctx=65536, c_max=1024, max_chunks=max_chunks)]
         assert (len(names) == 1 and "select_attention" in names[0]) == fused, (budget, max_chunks, names)
         assert ("topk_select" in names[0]) != fused, names
+
+
+@pytest.mark.parametrize("G,units,budget,max_chunks,fused", [
+    # one round: uneven lists, little more than half as many as compute units
+    (1, 128, 0, 512, True), (1, 129, 0, 512, False), (1, 152, 0, 16, False), (1, 152, 0, 15, True), (1, 153, 0, 512, True),
+    (2, 140, 0, 32, False), (2, 140, 0, 31, True), (2, 141, 0, 512, True), (4, 129, 0, 512, True), (1, 129, 8192, 0, True),
+    (1, 256, 8192, 0, True),
+    # two and three rounds: few workgroups in the last
+    (1, 257, 192, 0, False), (1, 257, 191, 0, True), (1, 384, 8192, 0, False), (1, 385, 8192, 0, True),
+    (2, 257, 384, 0, False), (2, 257, 383, 0, True), (2, 336, 8192, 0, False), (2, 337, 8192, 0, True),
+    (4, 257, 768, 0, False), (4, 257, 767, 0, True), (4, 288, 8192, 0, False), (4, 289, 8192, 0, True),
+    (1, 512, 64, 0, True), (1, 513, 200, 0, False), (1, 640, 8192, 0, False), (1, 641, 97, 0, True), (1, 641, 96, 0, False),
+    (2, 513, 97, 0, True), (2, 768, 96, 0, False), (4, 768, 64, 0, True),
+    # more rounds: short lists
+    (1, 769, 512, 0, False), (1, 769, 513, 0, True), (2, 1100, 256, 0, False), (2, 1100, 257, 0, True),
+    (4, 800, 96, 0, False), (4, 800, 97, 0, True)])
+def test_fp32_leaves_the_one_launch_kernel_where_it_would_wait_for_few_workgroups(L, kernels_of, G, units, budget, max_chunks, fused):
+    names = [n for n, _ in one_call(L, kernels_of, "f32", G, units, budget, n_ctx=65536, c_max=1024, max_chunks=max_chunks)]
+    assert (len(names) == 1 and "select_attention" in names[0]) == fused, names
+    assert ("topk_select" in names[0]) != fused, names
+    assert len(one_call(L, kernels_of, "f16", G, units, budget, n_ctx=65536, c_max=1024, max_chunks=max_chunks)) == 1
 
 
 @pytest.mark.parametrize("dtype,G,units,m0,apart", [
