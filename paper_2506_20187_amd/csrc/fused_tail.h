@@ -106,8 +106,9 @@ __device__ __forceinline__ void fused_tail(float (*xw)[kHeads][kPartStride], int
         const float* base = partial + bj * (size_t)stride * kPartStride;
         state = FoldedState{};
         // a batch of partials is one memory round trip: (m, l) of a split per lane, its column from each
-        auto merge_batch = [&](int s0, auto width) {
+        auto merge_batch = [&](int s0, auto width, auto full) {
             constexpr int kW = decltype(width)::value;
+            constexpr bool kFull = decltype(full)::value;
             const int own = s0 + (lane_id() & (kFusedMergeBatch - 1));
             const bool real = own < n_splits && own < s0 + kW;
             const unsigned long long ml = __hip_atomic_load(
@@ -116,20 +117,25 @@ __device__ __forceinline__ void fused_tail(float (*xw)[kHeads][kPartStride], int
             float os[kW];
 #pragma unroll
             for (int i = 0; i < kW; ++i)
-                os[i] = __hip_atomic_load(&base[(size_t)min(s0 + i, n_splits - 1) * kPartStride + d], __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
+                os[i] = __hip_atomic_load(&base[(size_t)(kFull ? s0 + i : min(s0 + i, n_splits - 1)) * kPartStride + d],
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (!kFull) {      // past the end the weight is 0, but the last split's value may be infinite
 #pragma unroll
-            for (int i = 0; i < kW; ++i)      // (past the end the weight is 0, the last split's value may be infinite)
-                if (s0 + i >= n_splits) os[i] = 0.f;
+                for (int i = 0; i < kW; ++i)
+                    if (s0 + i >= n_splits) os[i] = 0.f;
+            }
             state.fold<kW>(real ? bits_to_float((uint32_t)ml) : -INFINITY, real ? bits_to_float((uint32_t)(ml >> 32)) : 0.f,
                            [&](int i) { return os[i]; });
         };
         if (n_splits <= 4) {
-            merge_batch(0, std::integral_constant<int, 4>{});
+            merge_batch(0, std::integral_constant<int, 4>{}, std::false_type{});
         } else if (n_splits <= 8) {
-            merge_batch(0, std::integral_constant<int, 8>{});
+            merge_batch(0, std::integral_constant<int, 8>{}, std::false_type{});
         } else {
-            for (int s0 = 0; s0 < n_splits; s0 += kFusedMergeBatch) merge_batch(s0, std::integral_constant<int, kFusedMergeBatch>{});
+            const std::integral_constant<int, kFusedMergeBatch> width{};
+            int s0 = 0;
+            for (; s0 + width() <= n_splits; s0 += width()) merge_batch(s0, width, std::true_type{});
+            if (s0 < n_splits) merge_batch(s0, width, std::false_type{});
         }
         m = state.m;
         l = state.l;
