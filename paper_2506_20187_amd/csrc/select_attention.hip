@@ -451,8 +451,9 @@ bool select_attention_is_fused(const leoam_shape* s) {
     return s->kv_dtype != LEOAM_Q8Q4 && s->k_max <= kFusedMaxSel && s->c_max <= 8 * kSelThreads &&
            s->n_ctx < (s->kv_dtype == LEOAM_F32 ? 1 << 23 : 1 << 24);
 }
-// the shapes whose two-split launches merge through exchange words
-static inline bool has_exchange(const leoam_shape* s) {
+// The shapes of which every call runs in one launch (the others: where one_launch_pays says so).  Their two-split
+// launches merge through exchange words, and with a single split they need no room for partials.
+static inline bool always_one_launch(const leoam_shape* s) {
     return select_attention_is_fused(s) && s->kv_dtype != LEOAM_F32 && s->n_q_heads / s->n_kv_heads <= kFusedHeads;
 }
 
@@ -478,7 +479,7 @@ static int fused_recommended_splits(const leoam_shape* s, int max_tokens) {
 // (b, h), i.e. between half a workgroup and one workgroup per compute unit.
 static inline size_t exchange_bytes(const leoam_shape* s) {
     const long long units = (long long)s->batch * s->n_kv_heads;
-    if (!has_exchange(s) || (kFusedTargetWgs + units - 1) / units != 2) return 0;
+    if (!always_one_launch(s) || (kFusedTargetWgs + units - 1) / units != 2) return 0;
     return (size_t)s->batch * s->n_q_heads * LEOAM_D * sizeof(unsigned long long);
 }
 
@@ -505,7 +506,8 @@ size_t select_attention_workspace_bytes(const leoam_shape* s, int max_tokens, bo
 size_t select_attention_counter_bytes(const leoam_shape* s, bool with_exchange) { return control_bytes(s, with_exchange); }
 
 size_t select_attention_min_workspace_bytes(const leoam_shape* s, bool with_exchange) {
-    const bool one_launch = (has_exchange(s) || select_attention_q_is_fused(s)) && !stream_ordered_merge_wanted();
+    // (the separate kernels need one partial per (b, q head), and which calls take them is not known from the shape)
+    const bool one_launch = (always_one_launch(s) || select_attention_q_is_fused(s)) && !stream_ordered_merge_wanted();
     return control_bytes(s, with_exchange) + (one_launch ? 0 : attention_min_workspace_bytes(s));
 }
 
