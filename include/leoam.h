@@ -257,14 +257,17 @@ int sparse_chunk_attention_decode(const leoam_shape* shape, const void* q, const
  * chunk_topk_select followed by sparse_chunk_attention_decode (Sec. 4.2 / 6.1,
  * then Sec. 2.1 Eq. (1) over the kept chunks; Sec. 4.1: the evaluation result
  * selects the KV the decoding computation uses), with the same arguments,
- * outputs and preconditions as those two calls.  For fp16 / bf16 K and V with
- * group size <= 4, k_max <= 2048 and c_max <= 8192 both steps run in a single
- * kernel: every workgroup selects for its (b,h), keeps the kept chunks' token
- * ranges on chip and streams its share of the kept tokens; workgroups that share
- * a (b,h) combine their partials in the same launch, in split order, so results
- * do not depend on scheduling.  Other shapes run the two kernels of the separate
- * calls back to back.  sel_idx / sel_count / sel_tokens are written as by
- * chunk_topk_select.
+ * outputs and preconditions as those two calls.  With k_max <= 2048,
+ * c_max <= 8192 and n_ctx < 2^24 (fp32: 2^23; LEOAM_Q8Q4: group size <= 4 and
+ * k_max <= 1024 instead) both steps run in a single kernel: every workgroup
+ * selects for its (b,h), keeps the kept chunks' token ranges on chip and streams
+ * its share of the kept tokens; workgroups that share a (b,h) combine their
+ * partials in the same launch, in split order, so results do not depend on
+ * scheduling.  Other shapes, and those fp32 and group-of-eight calls that are
+ * faster there (by the number of (b,h) pairs and of tokens to keep), run the two
+ * kernels of the separate calls back to back; up to 16 splits are then merged by
+ * the attention kernel in the same way.  sel_idx / sel_count / sel_tokens are
+ * written as by chunk_topk_select.
  * With LEOAM_STREAM_ORDERED_MERGE=1 in the environment (read once per process)
  * every shape runs the kernels of the separate calls, merge kernel included:
  * the in-launch combination of the splits orders its hand-over by waiting for
@@ -283,9 +286,12 @@ int sparse_chunk_attention_decode(const leoam_shape* shape, const void* q, const
  * (b,h) pairs and, for batch sizes that give two splits per (b,h), one 64-bit
  * exchange word per (b, q head, channel)): they must be ZERO when the call is
  * issued and are zero again when it completes, so a workspace is cleared once
- * (leoam_workspace_init) and then reused; the rest needs no initialisation.  A
- * smaller workspace gives fewer splits.  Calls that share a workspace must not
- * overlap.
+ * (leoam_workspace_init) and then reused; the rest needs no initialisation.  The
+ * splits of a call fill one round of workgroups as far as the workspace holds
+ * their partials: a smaller one gives fewer splits.  The smallest is the control
+ * words and, but for shapes that always run in the single kernel (fp16 / bf16
+ * with group size <= 4, LEOAM_Q8Q4, within the limits above and without
+ * LEOAM_STREAM_ORDERED_MERGE), one partial per (b, q head) (520 bytes).  Calls that share a workspace must not overlap.
  */
 int chunk_select_attention_decode(const leoam_shape* shape, const float* score_ub, const void* q, const void* K,
                                   const void* V, const void* qmeta, const int32_t* chunk_off, const int32_t* n_chunks,
@@ -303,9 +309,9 @@ int chunk_select_attention_decode(const leoam_shape* shape, const float* score_u
  * nothing and frees nothing; it enqueues one small fill kernel (the counters) and
  * the kernels of chunk_select_attention_decode.  The number of splits is what
  * leoam_fused_workspace_bytes(shape, token_budget) would give, or fewer if that
- * exceeds the buffer; a shape whose smallest workspace does not fit (a two-launch
- * shape with batch * n_q_heads * 520 bytes above the limit, or more than 64 Ki
- * (sequence, kv head) pairs' counters) returns LEOAM_E_WORKSPACE and enqueues
+ * exceeds the buffer; a shape whose smallest workspace does not fit (a shape that
+ * does not always run in the single kernel, with batch * n_q_heads * 520 bytes
+ * and its counters above the limit) returns LEOAM_E_WORKSPACE and enqueues
  * nothing.  All calls on one GPU share the buffer: calls that may overlap on a
  * GPU (two streams, two threads) race and must be serialised by the caller.  The
  * buffer's address is looked up on the first call on each device (not inside a
