@@ -804,6 +804,34 @@ def test_one_call_keeps_infinite_values_apart(L, oracle, dtype, G):
             assert np.abs(lse - want_lse).max() <= 1e-4, tag
 
 
+@pytest.mark.parametrize("dtype,G", [("bf16", 4), ("f32", 1)])
+def test_one_call_merges_every_number_of_splits(L, oracle, kernels_of, dtype, G):
+    """Numbers of splits at the edges of the batches in which partials are merged (up to 4, up to 8, sixteens, a rest); the
+    last split, which fills up the last batch, is the only one with an infinite value."""
+    rng = np.random.default_rng(90 + G)
+    B, Hkv, D, chunk, N = 1, 2, 128, 32, 256 * 50
+    off = np.arange(0, N + 1, chunk, dtype=np.int32)
+    packed, counts, c_max = gen.pack_boundaries([off], N)
+    q = torch.from_numpy(rng.standard_normal((B, Hkv * G, D)).astype(np.float32)).to(TDT[dtype])
+    K, V = (torch.from_numpy(rng.standard_normal((B, Hkv, N, D)).astype(np.float32)).to(TDT[dtype]) for _ in range(2))
+    score = np.tile(np.arange(c_max, 0, -1, dtype=np.float32), (B, Hkv, 1))      # the first chunks are kept
+    for splits in (2, 3, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 48):
+        kept = 256 * splits - 96
+        sel, cnt, _ = oracle.topk_select(score, packed, counts, 0, kept, c_max)
+        v, ref = V.clone(), V.clone()
+        v[:, :, kept - 1, 0] = float("inf")
+        ref[..., 0] = 0
+        want, want_lse = oracle.sparse_attention(q, K, ref, packed, sel, cnt)
+        shape, t = L.make_shape(B, Hkv * G, Hkv, D, N, c_max, c_max, TDT[dtype]), torch.zeros(64, device="cuda")
+        ws = torch.zeros(L.leoam_fused_workspace_bytes(shape, kept) + 15 & ~15, dtype=torch.uint8, device="cuda")
+        (name, grid), = kernels_of(lambda: L.chunk_select_attention_decode(shape, t, t, t, t, t, t, 0, kept, 1.0, t, t, t, t, t, ws))
+        assert "select_attention_kernel" in name and grid == (splits, Hkv, B), (name, grid)
+        _, _, _, out, lse, _ = gpu_select_attend(L, dtype, score, q, K, v, packed, counts, 0, kept, c_max)
+        assert np.all(np.isposinf(out[..., 0])), splits
+        assert np.abs(out[..., 1:] - want[..., 1:]).max() <= TOL[dtype], splits
+        assert np.abs(lse - want_lse).max() <= 1e-4, splits
+
+
 @pytest.mark.parametrize("over", ["k_max", "c_max"])
 @pytest.mark.parametrize("dtype,G", [("bf16", 4), ("f16", 1), ("bf16", 8), ("f32", 1), ("f32", 4), ("f32", 8)])
 def test_one_call_over_the_tables_of_the_one_launch_kernel(L, oracle, kernels_of, dtype, G, over):
