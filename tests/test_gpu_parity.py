@@ -832,6 +832,33 @@ def test_one_call_merges_every_number_of_splits(L, oracle, kernels_of, dtype, G)
         assert np.abs(lse - want_lse).max() <= 1e-4, splits
 
 
+@pytest.mark.parametrize("dtype,n_ctx", [("bf16", (1 << 24) - 1), ("bf16", 1 << 24), ("f32", (1 << 23) - 1), ("f32", 1 << 23)])
+def test_one_call_at_the_largest_context_of_the_one_launch_kernel(L, kernels_of, dtype, n_ctx):
+    """4 GiB of keys of one kv head: the last context whose row offsets fit 32 bits in the one-launch kernel, and the next,
+    which takes the separate kernels.  The first, a middle and the last chunk are kept; all other rows hold NaN."""
+    Hq, D, C = 2, 128, 8000
+    off = torch.linspace(0, n_ctx - 37, C, dtype=torch.float64).to(torch.int32)
+    off = torch.cat([off, torch.tensor([n_ctx], dtype=torch.int32)])
+    keep = [0, 4000, C - 1]
+    rows = torch.cat([torch.arange(int(off[c]), int(off[c + 1])) for c in keep])
+    g = torch.Generator().manual_seed(n_ctx)
+    k, v = (torch.randn(len(rows), D, generator=g).to(TDT[dtype]) for _ in range(2))
+    q = torch.randn(1, Hq, D, generator=g).to(TDT[dtype])
+    K, V = (torch.full((1, 1, n_ctx, D), float("nan"), dtype=TDT[dtype], device="cuda") for _ in range(2))
+    K[0, 0, rows.cuda()], V[0, 0, rows.cuda()] = k.cuda(), v.cuda()
+    score = torch.zeros(1, 1, C)
+    score[0, 0, keep] = 1.0
+    shape, t = L.make_shape(1, Hq, 1, D, n_ctx, C, 4, TDT[dtype]), torch.zeros(64, device="cuda")
+    ws = torch.zeros(L.leoam_fused_workspace_bytes(shape, 0) + 15 & ~15, dtype=torch.uint8, device="cuda")
+    names = [n for n, _ in kernels_of(lambda: L.chunk_select_attention_decode(shape, t, t, t, t, t, t, 3, 0, 1.0, t, t, t, t, t, ws))]
+    assert ("select_attention_kernel" in names[0]) == (n_ctx not in (1 << 23, 1 << 24)), names
+    sel, cnt, _, out, lse, _ = gpu_select_attend(L, dtype, score, q, K, V, off[None], torch.tensor([C], dtype=torch.int32), 3, 0, 4)
+    assert sel[0, 0].tolist() == keep + [-1] and cnt[0, 0] == 3
+    z = q[0].double() @ k.double().T / D ** 0.5
+    assert np.abs(out[0] - (torch.softmax(z, 1) @ v.double()).numpy()).max() <= TOL[dtype]
+    assert np.abs(lse[0] - torch.logsumexp(z, 1).numpy()).max() <= 1e-4
+
+
 @pytest.mark.parametrize("over", ["k_max", "c_max"])
 @pytest.mark.parametrize("dtype,G", [("bf16", 4), ("f16", 1), ("bf16", 8), ("f32", 1), ("f32", 4), ("f32", 8)])
 def test_one_call_over_the_tables_of_the_one_launch_kernel(L, oracle, kernels_of, dtype, G, over):
